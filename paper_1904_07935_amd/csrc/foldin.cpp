@@ -54,9 +54,8 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
   f.S = c.take<float>((size_t)K * K);
   f.Qn = c.take<float>((size_t)K * K);
   size_t part = 1;
-  int64_t kps;
   if (AnewT->format == NMF_DENSE) {
-    const int sp = gemm_pick_splits(Dn, K, V, &kps);
+    const int sp = gemm_plan(Elem::F32, Dn, K, V).splits;
     if (sp > 1) part = std::max(part, (size_t)sp * Dn * K);
   }
   f.partial = c.take<float>(part);
@@ -210,7 +209,7 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
     g.C = f.R;
     g.ldc = K;
     g.epi = EPI_STORE;
-    g.splits = gemm_pick_splits(g.M, g.N, g.Kd, &g.k_per_split);
+    gemm_use(g, gemm_plan(Elem::F32, g.M, g.N, g.Kd));
     g.partial = f.partial;
     FCHECK(gemm(Elem::F32, false, false, g, s));
     const int nb = reduce_blocks(Dn * p->V);

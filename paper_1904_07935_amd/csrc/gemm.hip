@@ -1,20 +1,37 @@
 // Matrix-core GEMM for gfx950: C = op(A) op(B) with FP32 accumulation.
 //
 // Used for every dense product of the sweep (A H^T and A^T W on dense A, Alg. 1
-// statements forming R and P), the Gram matrices W^T W and H H^T (the S and Q
-// statements of Alg. 1), the dense residual of the objective (Eq. 2), and the
-// warm-start network's forward and backward products.
+// statements forming R and P), the dense-row block of P on sparse A, the dense
+// residual of the objective (Eq. 2), the multiplicative updates' denominators,
+// and the warm-start network's forward and backward products.
 //
-// Tiles of 128 x 128 per workgroup, four wave64s in a 2 x 2 arrangement, each
-// owning 64 x 64 = 2 x 2 blocks of the 32 x 32 MFMA output.  Operands are staged
-// through double-buffered LDS in the layout each MFMA variant reads with
-// conflict-light unit-stride lane access:
-//   FP32  v_mfma_f32_32x32x2_f32   lane l supplies A[l%32][l/32], B[l/32][l%32]
-//         -> LDS k-major: As[k][m], Bs[k][n]; BK = 16
-//   BF16  v_mfma_f32_32x32x16_bf16 lane l supplies A[l%32][8(l/32)..+7] and
-//         B[8(l/32)..+7][l%32] -> LDS k-contiguous: As[m][k], Bs[n][k]; BK = 32
-// Output block layout (both): lane l holds C[8j + 4(l/32) + i][l%32], j,i < 4.
+// FP32 operands run on the BF16 matrix cores.  Each FP32 value is split into
+// three BF16 parts that add up to it exactly (8 + 8 + 8 significand bits), and
+// a product x y is the sum of the six part products of order 2^-16 and above:
+// xh yh + (xh ym + xm yh) + (xh yl + xm ym + xl yh).  What is left out, xm yl +
+// xl ym + xl yl, is at most a few units of 2^-24 of the product and of either
+// sign, like one FP32 rounding.  Six v_mfma_f32_32x32x16_bf16 cover 16 terms in
+// 192 cycles per 32 x 32 block; eight v_mfma_f32_32x32x2_f32 take 512.
+//
+// One operand layout serves both element types: lane l of the 32x32x16 product
+// supplies A[l%32][8(l/32)..+7] and B[8(l/32)..+7][l%32], so a tile is staged in
+// LDS as 16-byte chunks of 8 consecutive contraction terms, chunk (part, k/8,
+// row) at [part][k/8][row]: a wave's operand read is 32 consecutive chunks per
+// half, without bank conflicts, whichever way the operand lies in memory.  The
+// split runs once per element on the way from registers to LDS.
+// Output block layout: lane l holds C[8j + 4(l/32) + i][l%32], j,i < 4.
 // Split-K writes FP32 partials that a fixed-order pass sums (deterministic).
+//
+// What bounds it and what it measured (against the 128 x 128 kernel on the FP32
+// matrix cores that it replaced; same box): 10,000 x 240 x 10,000 FP32 550 ->
+// 330 us per product, with the splitting (about 5.5 VALU instructions per
+// element) and the matrix cores each near half of the time; the dense-row block
+// (256 x 400 x 300,000) 715 -> 430 us; BF16 10,000 x 240 x 10,000 121 -> 80 us,
+// bound by the latency of the operand loads; 800 x 16 x 1,000 35 -> 10 us and
+// 4,096 x 100 x 100 17 -> 7.5 us, latency (small tiles, more splits).  Errors
+// against 64 bits, RMS over sampled elements, old / new: 9.5e-8 / 9.5e-8 at
+// 10,000 terms, 6.0e-8 / 4.7e-8 at 100, 1.3e-7 / 1.3e-7 at 300,000.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -23,26 +40,95 @@
 namespace plnmf {
 namespace {
 
-constexpr int BM = 128, BN = 128;
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Workgroup tiles.  BM x BN outputs by waves of 32 BI x 32 BJ; BK32 / BK16 terms
+// of FP32 / BF16 operands per K-step; one LDS buffer, so that more workgroups
+// fit on a CU and one's staging overlaps another's products, or two.
+template <int CFG>
+struct Tile;
+template <>
+struct Tile<0> {  // large products
+  static constexpr int BM = 128, BN = 128, BI = 2, BJ = 2, BK32 = 32, BK16 = 64, BUFS = 1;
+};
+template <>
+struct Tile<1> {  // few outputs: more workgroups
+  static constexpr int BM = 64, BN = 64, BI = 1, BJ = 1, BK32 = 32, BK16 = 64, BUFS = 1;
+};
+template <>
+struct Tile<2> {  // at most 32 columns
+  static constexpr int BM = 128, BN = 32, BI = 1, BJ = 1, BK32 = 32, BK16 = 64, BUFS = 2;
+};
+template <int CFG>
+constexpr int threads_of() {
+  return 64 * (Tile<CFG>::BM / (32 * Tile<CFG>::BI)) * (Tile<CFG>::BN / (32 * Tile<CFG>::BJ));
+}
+template <typename T, int CFG>
+constexpr int bk_of() {
+  return sizeof(T) == 4 ? Tile<CFG>::BK32 : Tile<CFG>::BK16;
+}
+template <typename T>
+constexpr int parts_of() {
+  return sizeof(T) == 4 ? 3 : 1;
+}
+// LDS rows of a chunk plane: padded so that the eight lanes of one write cycle
+// (consecutive k/8 of one or two rows) fall on different banks
+template <int R, int BK>
+constexpr int pitch_of() {
+  return R + (BK >= 64 ? 1 : BK == 32 ? 2 : 4);
+}
+template <typename T, int CFG>
+constexpr size_t lds_bytes_of() {
+  constexpr int BK = bk_of<T, CFG>();
+  return (size_t)Tile<CFG>::BUFS * parts_of<T>() * (BK / 8) *
+         (pitch_of<Tile<CFG>::BM, BK>() + pitch_of<Tile<CFG>::BN, BK>()) * 16;
+}
 
 // Operand tiles are read through buffer descriptors whose base is the step's
 // tile origin.  A lane whose element lies outside the matrix (a row past M or
 // N, a term past the end of its split) uses an offset past the descriptor's
 // range, and the hardware returns zeros for it without touching memory: no
-// branches, so the loads of a step issue back to back and the wait before the
-// LDS store counts them exactly.  Valid offsets stay below 2^31 bytes (the
-// host routes leading dimensions of 2^22 or more to the scalar path).
+// branches, so the loads of a step issue back to back.  Valid offsets stay
+// below 2^31 bytes (leading dimensions of 2^22 or more, and BF16 rows that are
+// not 4-byte aligned, take the element-wise path).
 constexpr uint32_t kOutside = 0x80000000u;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_view(const void* base, int64_t bytes) {
   const int64_t n = bytes < 0 ? 0 : (bytes > 0x7fffffff ? 0x7fffffff : bytes);
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, 0x00020000);
 }
-__device__ __forceinline__ floatx4 ld4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+__device__ __forceinline__ uintx4 ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
-__device__ __forceinline__ bf16x8 ld8h(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+__device__ __forceinline__ unsigned ld4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+}
+
+__device__ __forceinline__ unsigned hi_halves(unsigned lo, unsigned hi) {
+  return __builtin_amdgcn_perm(hi, lo, 0x07060302);
+}
+__device__ __forceinline__ unsigned lo_halves(unsigned lo, unsigned hi) {
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100);
+}
+
+// Eight FP32 values into their three BF16 parts, packed.  The high part is the
+// value cut to BF16 (so that no finite value rounds up to infinity), the middle
+// part the rest rounded to nearest, the low part what remains (exact).
+__device__ __forceinline__ void split8(const unsigned (&x)[8], uintx4& ph, uintx4& pm, uintx4& pl) {
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const unsigned u0 = x[2 * q], u1 = x[2 * q + 1];
+    ph[q] = hi_halves(u0, u1);
+    const floatx2 r = {__uint_as_float(u0) - __uint_as_float(u0 & 0xffff0000u),
+                       __uint_as_float(u1) - __uint_as_float(u1 & 0xffff0000u)};
+    const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
+    pm[q] = m;
+    const float l0 = r[0] - __uint_as_float(m << 16);
+    const float l1 = r[1] - __uint_as_float(m & 0xffff0000u);
+    pl[q] = hi_halves(__float_as_uint(l0), __float_as_uint(l1));
+  }
 }
 
 __device__ __forceinline__ float gelu_grad_f(float z) {
@@ -51,25 +137,169 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
   return cdf + z * pdf;
 }
 
-// Epilogue over one wave's 2 x 2 blocks.  `acc[i][j]` is the 32x32 block at
-// rows r0 + 32 i, cols c0 + 32 j.  Every field is passed by value so nothing
-// here takes the address of the kernel argument block.  The epilogue kind and
-// whether the wave's 64 x 64 block lies wholly inside C are template
-// parameters: each instantiation is one straight run of 64 element updates,
-// with no per-element dispatch on the kind and, inside C, no bounds checks.
-template <int EPI, bool FULL>
+// Global -> register -> LDS staging of one K-step of one operand: R rows (of A,
+// or columns of B) by BK terms.  TR: the rows are contiguous in memory (a dword
+// per lane, consecutive lanes along the rows), else the terms are (16 bytes per
+// lane).  FAR: element-wise loads at 64-bit addresses, any alignment.
+template <typename T, bool TR, bool FAR, int R, int BK, int NTHR>
+struct Stage {
+  static constexpr int K8 = BK / 8, RP = pitch_of<R, BK>();
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr bool PAIR = !F32 && TR && !FAR;  // a dword holds two rows of a term
+  static constexpr int ITEMS = PAIR ? R / 2 * K8 : R * K8;
+  static constexpr int NI = (ITEMS + NTHR - 1) / NTHR;
+  static constexpr int REGS = F32 || PAIR ? 8 : 4;
+  unsigned v[NI][REGS];
+  uint32_t off[NI];  // byte offset of each item's first element from a step's tile origin
+
+  static __device__ __forceinline__ void place(int i, int tid, int& r, int& k8, bool& in) {
+    const int c = tid + NTHR * i;
+    in = ITEMS % NTHR == 0 || c < ITEMS;
+    if constexpr (PAIR) {
+      r = 2 * (c % (R / 2));
+      k8 = c / (R / 2);
+    } else if constexpr (TR) {
+      r = c % R;
+      k8 = c / R;
+    } else {
+      r = c / K8;
+      k8 = c % K8;
+    }
+  }
+
+  __device__ __forceinline__ void init(int64_t ld, int64_t rows, int64_t r0, int tid) {
+    if constexpr (!FAR) {
+#pragma unroll
+      for (int i = 0; i < NI; i++) {
+        int r, k8;
+        bool in;
+        place(i, tid, r, k8, in);
+        off[i] = in && r < rows - r0
+                     ? (uint32_t)((TR ? 8 * k8 * ld + r : r * ld + 8 * k8) * (int64_t)sizeof(T))
+                     : kOutside;
+      }
+    }
+  }
+
+  __device__ __forceinline__ void load(const T* __restrict__ X, int64_t ld, int64_t rows, int64_t r0,
+                                       int64_t k0, int64_t ke, int64_t Kd, int tid) {
+    const int rem = ke - k0 >= BK ? BK : (ke > k0 ? (int)(ke - k0) : 0);
+    if constexpr (FAR) {
+      const int left = rows - r0 >= R ? R : (int)(rows - r0);
+#pragma unroll
+      for (int i = 0; i < NI; i++) {
+        int r, k8;
+        bool in;
+        place(i, tid, r, k8, in);
+        T e[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+          const bool ok = in && r < left && 8 * k8 + q < rem;
+          const int64_t kk = k0 + 8 * k8 + q;
+          e[q] = ok ? (TR ? X[kk * ld + r0 + r] : X[(r0 + r) * ld + kk]) : (T)0.0f;
+        }
+        if constexpr (F32) {
+#pragma unroll
+          for (int q = 0; q < 8; q++) v[i][q] = __builtin_bit_cast(unsigned, e[q]);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+            v[i][q] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)e[2 * q], (__bf16)e[2 * q + 1]});
+        }
+      }
+    } else {
+      constexpr int ES = sizeof(T);
+      const int64_t o = TR ? k0 * ld + r0 : r0 * ld + k0;
+      // one past the last element; an odd last BF16 row (column) is followed by
+      // its padding element
+      const int64_t wide = F32 ? 0 : 1;
+      const int64_t end = TR ? (Kd - 1) * ld + ((rows + wide) & ~wide)
+                             : (rows - 1) * ld + ((Kd + wide) & ~wide);
+      const __amdgpu_buffer_rsrc_t view = tile_view(X + o, (end - o) * ES);
+      const uint32_t st = (uint32_t)(ld * ES);
+      if (rem == BK) {
+        // every term in range: one vector offset per item, the rest scalar
+#pragma unroll
+        for (int i = 0; i < NI; i++) {
+          if constexpr (TR) {
+#pragma unroll
+            for (int q = 0; q < 8; q++)
+              v[i][q] = __builtin_amdgcn_raw_buffer_load_b32(view, off[i], q * st, 0);
+          } else {
+#pragma unroll
+            for (int q = 0; q < REGS / 4; q++) {
+              const uintx4 x = ld16(view, off[i] + 16 * q);
+#pragma unroll
+              for (int e = 0; e < 4; e++) v[i][4 * q + e] = x[e];
+            }
+          }
+        }
+      } else {
+        // the ragged last step: dword by dword, terms past the end cleared
+#pragma unroll
+        for (int i = 0; i < NI; i++) {
+          int r, k8;
+          bool in;
+          place(i, tid, r, k8, in);
+          constexpr int PER = TR ? 1 : 4 / ES;
+#pragma unroll
+          for (int q = 0; q < REGS; q++) {
+            const int k = 8 * k8 + PER * q;
+            unsigned x = ld4(view, off[i] != kOutside && k < rem ? off[i] + (TR ? q * st : 4u * q) : kOutside);
+            if (!F32 && !TR && k + 1 >= rem) x &= 0xffffu;
+            v[i][q] = x;
+          }
+        }
+      }
+    }
+  }
+
+  __device__ __forceinline__ void store(uintx4* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+      int r, k8;
+      bool in;
+      place(i, tid, r, k8, in);
+      if (!in) continue;
+      uintx4* d = lds + k8 * RP + r;
+      if constexpr (F32) {
+        uintx4 h, m, l;
+        split8(v[i], h, m, l);
+        d[0] = h;
+        d[K8 * RP] = m;
+        d[2 * K8 * RP] = l;
+      } else if constexpr (PAIR) {
+        uintx4 a, b;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          a[q] = lo_halves(v[i][2 * q], v[i][2 * q + 1]);
+          b[q] = hi_halves(v[i][2 * q], v[i][2 * q + 1]);
+        }
+        d[0] = a;
+        d[1] = b;
+      } else {
+        d[0] = uintx4{v[i][0], v[i][1], v[i][2], v[i][3]};
+      }
+    }
+  }
+};
+
+// Epilogue over one wave's BI x BJ blocks.  `acc[i][j]` is the 32x32 block at
+// rows r0 + 32 i, cols c0 + 32 j.  The epilogue kind and whether the wave's
+// block lies wholly inside C are template parameters: each instantiation is
+// one straight run of element updates, with no per-element dispatch on the kind
+// and, inside C, no bounds checks.
+template <int EPI, bool FULL, int BI, int BJ>
 __device__ __forceinline__ void epi_block(int64_t M, int64_t N, float* __restrict__ out,
-                                          int64_t ldo, bool split, const float* __restrict__ bias,
-                                          const float* Dm, int64_t ldd, void* __restrict__ C2,
-                                          float* C, int64_t ldc, floatx16 (&acc)[2][2],
-                                          int64_t r0, int64_t c0, bool mirror, float mu_delta,
-                                          double& ss) {
+                                          int64_t ldo, const float* __restrict__ bs,
+                                          const float* Dm, int64_t ldd, void* C2, float* C,
+                                          int64_t ldc, floatx16 (&acc)[BI][BJ], int64_t r0,
+                                          int64_t c0, float mu_delta, double& ss) {
   const int lane = threadIdx.x & 63;
-  const float* bs = (EPI != EPI_STORE || !split) ? bias : nullptr;
 #pragma unroll
-  for (int i = 0; i < 2; i++)
+  for (int i = 0; i < BI; i++)
 #pragma unroll
-    for (int j = 0; j < 2; j++)
+    for (int j = 0; j < BJ; j++)
 #pragma unroll
       for (int jj = 0; jj < 4; jj++)
 #pragma unroll
@@ -77,11 +307,9 @@ __device__ __forceinline__ void epi_block(int64_t M, int64_t N, float* __restric
           const int64_t m = r0 + 32 * i + 8 * jj + 4 * (lane >> 5) + ii;
           const int64_t n = c0 + 32 * j + (lane & 31);
           if (!FULL && (m >= M || n >= N)) continue;
-          float v = acc[i][j][jj * 4 + ii];
+          const float v = acc[i][j][jj * 4 + ii];
           if constexpr (EPI == EPI_STORE) {
-            if (bs) v += bs[n];
-            out[m * ldo + n] = v;
-            if (mirror) out[n * ldo + m] = v;  // symmetric product, tile above the diagonal
+            out[m * ldo + n] = bs ? v + bs[n] : v;
           } else if constexpr (EPI == EPI_RESID_SQ) {
             const float e = Dm[m * ldd + n] - v;
             ss += (double)e * (double)e;
@@ -104,52 +332,13 @@ __device__ __forceinline__ void epi_block(int64_t M, int64_t N, float* __restric
         }
 }
 
-template <int EPI>
-__device__ __forceinline__ void epi_kind(int64_t M, int64_t N, float* __restrict__ out,
-                                         int64_t ldo, bool split, const float* __restrict__ bias,
-                                         const float* Dm, int64_t ldd, void* __restrict__ C2,
-                                         float* C, int64_t ldc, floatx16 (&acc)[2][2], int64_t r0,
-                                         int64_t c0, bool mirror, float mu_delta, double& ss) {
-  if (r0 + 64 <= M && c0 + 64 <= N)
-    epi_block<EPI, true>(M, N, out, ldo, split, bias, Dm, ldd, C2, C, ldc, acc, r0, c0, mirror,
-                         mu_delta, ss);
-  else
-    epi_block<EPI, false>(M, N, out, ldo, split, bias, Dm, ldd, C2, C, ldc, acc, r0, c0, mirror,
-                          mu_delta, ss);
-}
-
-__device__ __forceinline__ void epilogue(int epi, int64_t M, int64_t N, float* __restrict__ out,
-                                         int64_t ldo, bool split, const float* __restrict__ bias,
-                                         const float* Dm, int64_t ldd,
-                                         void* __restrict__ C2, float* C,
-                                         int64_t ldc, double* __restrict__ red_out,
-                                         floatx16 (&acc)[2][2], int64_t r0, int64_t c0,
-                                         double* red_smem, bool mirror, float mu_delta,
-                                         int64_t red_slot) {
-  double ss = 0.0;
-#define PLNMF_EPI(K)                                                                        \
-  epi_kind<K>(M, N, out, ldo, split, bias, Dm, ldd, C2, C, ldc, acc, r0, c0, mirror, mu_delta, \
-              ss)
-  switch (epi) {
-    case EPI_STORE: PLNMF_EPI(EPI_STORE); break;
-    case EPI_RESID_SQ: PLNMF_EPI(EPI_RESID_SQ); break;
-    case EPI_BIAS_GELU: PLNMF_EPI(EPI_BIAS_GELU); break;
-    case EPI_BIAS_SOFTPLUS: PLNMF_EPI(EPI_BIAS_SOFTPLUS); break;
-    case EPI_GELU_GRAD: PLNMF_EPI(EPI_GELU_GRAD); break;
-    case EPI_MU: PLNMF_EPI(EPI_MU); break;
-  }
-#undef PLNMF_EPI
-  if (epi == EPI_RESID_SQ) {
-    const int lane = threadIdx.x & 63;
-    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-    const int w = threadIdx.x >> 6;
-    if (lane == 0) red_smem[w] = ss;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const double t = red_smem[0] + red_smem[1] + red_smem[2] + red_smem[3];
-      red_out[red_slot] = t;
-    }
-  }
+// The epilogues each operand form is used with.
+template <typename T, bool AT, bool BT>
+__host__ __device__ constexpr bool epi_used(int epi) {
+  if (epi == EPI_STORE) return true;
+  if (sizeof(T) == 4) return (epi == EPI_MU && !AT && !BT) || (epi == EPI_RESID_SQ && !AT && BT);
+  if (!AT && BT) return epi == EPI_BIAS_GELU || epi == EPI_BIAS_SOFTPLUS;
+  return epi == EPI_GELU_GRAD && !AT && !BT;
 }
 
 // XCD-aware tile order.  Workgroups go to the eight XCDs round robin by
@@ -168,433 +357,335 @@ __device__ __forceinline__ void tile_of(int& tx, int& ty, int& tz) {
   tz = (int)(t / (gx * gy));
 }
 
-// Global -> register -> LDS staging of one K-step of the A and B tiles.
-template <typename T, bool AT, bool BT, bool VEC, int BK>
-struct Stage;
-
-// FP32: As[k][m], Bs[k][n] (k-major), BK = 16
-template <bool AT, bool BT, bool VEC>
-struct Stage<float, AT, BT, VEC, 16> {
-  static constexpr int LDS_A = BM + 4, LDS_B = BN + 4;
-  floatx4 ra[2], rb[2];
-  float sa[8], sb[8];
-  __device__ __forceinline__ void load(const float* __restrict__ A, const float* __restrict__ B,
-                                       int64_t lda, int64_t ldb, int64_t M, int64_t N,
-                                       int64_t m0, int64_t n0, int64_t k0, int64_t ke, int64_t Kd,
-                                       int tid) {
-    if constexpr (VEC) {
-      // this step's tile origin in each operand (wave-uniform), and the bytes
-      // from there to the operand's last element
-      const int64_t a0 = AT ? k0 * lda + m0 : m0 * lda + k0;
-      const int64_t b0 = BT ? n0 * ldb + k0 : k0 * ldb + n0;
-      const int64_t a_end = AT ? (Kd - 1) * lda + M : (M - 1) * lda + Kd;
-      const int64_t b_end = BT ? (N - 1) * ldb + Kd : (Kd - 1) * ldb + N;
-      const __amdgpu_buffer_rsrc_t va = tile_view(A + a0, (a_end - a0) * 4);
-      const __amdgpu_buffer_rsrc_t vb = tile_view(B + b0, (b_end - b0) * 4);
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int idx = tid + 256 * p;
-        if constexpr (!AT) {  // along k
-          const int ml = idx >> 2, kq = idx & 3;
-          const bool ok = m0 + ml < M && k0 + 4 * kq < ke;
-          ra[p] = ld4(va, ok ? (uint32_t)(ml * lda + 4 * kq) * 4u : kOutside);
-        } else {  // along m
-          const int kl = idx >> 5, mq = idx & 31;
-          const bool ok = m0 + 4 * mq < M && k0 + kl < ke;
-          ra[p] = ld4(va, ok ? (uint32_t)(kl * lda + 4 * mq) * 4u : kOutside);
-        }
-        if constexpr (!BT) {  // along n
-          const int kl = idx >> 5, nq = idx & 31;
-          const bool ok = n0 + 4 * nq < N && k0 + kl < ke;
-          rb[p] = ld4(vb, ok ? (uint32_t)(kl * ldb + 4 * nq) * 4u : kOutside);
-        } else {  // along k
-          const int nl = idx >> 2, kq = idx & 3;
-          const bool ok = n0 + nl < N && k0 + 4 * kq < ke;
-          rb[p] = ld4(vb, ok ? (uint32_t)(nl * ldb + 4 * kq) * 4u : kOutside);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        const int idx = tid + 256 * e;           // element of the 128 x 16 tile
-        const int kl = idx & 15, ml = idx >> 4;  // k fastest
-        const int64_t k = k0 + kl;
-        const int64_t m = m0 + ml, n = n0 + ml;
-        sa[e] = (m < M && k < ke) ? (AT ? A[k * lda + m] : A[m * lda + k]) : 0.0f;
-        sb[e] = (n < N && k < ke) ? (BT ? B[n * ldb + k] : B[k * ldb + n]) : 0.0f;
-      }
-    }
-  }
-  __device__ __forceinline__ void store(float (*As)[LDS_A], float (*Bs)[LDS_B], int tid) {
-    if constexpr (VEC) {
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int idx = tid + 256 * p;
-        if constexpr (!AT) {
-          const int ml = idx >> 2, kq = idx & 3;
-#pragma unroll
-          for (int e = 0; e < 4; e++) As[4 * kq + e][ml] = ra[p][e];
-        } else {
-          const int kl = idx >> 5, mq = idx & 31;
-          *(floatx4*)&As[kl][4 * mq] = ra[p];
-        }
-        if constexpr (!BT) {
-          const int kl = idx >> 5, nq = idx & 31;
-          *(floatx4*)&Bs[kl][4 * nq] = rb[p];
-        } else {
-          const int nl = idx >> 2, kq = idx & 3;
-#pragma unroll
-          for (int e = 0; e < 4; e++) Bs[4 * kq + e][nl] = rb[p][e];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        const int idx = tid + 256 * e;
-        const int kl = idx & 15, ml = idx >> 4;
-        As[kl][ml] = sa[e];
-        Bs[kl][ml] = sb[e];
-      }
-    }
-  }
-};
-
-// BF16: As[m][k], Bs[n][k] (k-contiguous), BK = 32
-template <bool AT, bool BT, bool VEC>
-struct Stage<__bf16, AT, BT, VEC, 32> {
-  static constexpr int LDS_K = 32 + 8;  // 80-byte rows keep 16-byte alignment
-  bf16x8 ra[2], rb[2];
-  __bf16 sa[16], sb[16];
-  __device__ __forceinline__ void load(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
-                                       int64_t lda, int64_t ldb, int64_t M, int64_t N,
-                                       int64_t m0, int64_t n0, int64_t k0, int64_t ke, int64_t Kd,
-                                       int tid) {
-    if constexpr (VEC) {
-      const int64_t a0 = AT ? k0 * lda + m0 : m0 * lda + k0;
-      const int64_t b0 = BT ? n0 * ldb + k0 : k0 * ldb + n0;
-      const int64_t a_end = AT ? (Kd - 1) * lda + M : (M - 1) * lda + Kd;
-      const int64_t b_end = BT ? (N - 1) * ldb + Kd : (Kd - 1) * ldb + N;
-      const __amdgpu_buffer_rsrc_t va = tile_view(A + a0, (a_end - a0) * 2);
-      const __amdgpu_buffer_rsrc_t vb = tile_view(B + b0, (b_end - b0) * 2);
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int idx = tid + 256 * p;
-        if constexpr (!AT) {
-          const int ml = idx >> 2, kq = idx & 3;
-          const bool ok = m0 + ml < M && k0 + 8 * kq < ke;
-          ra[p] = ld8h(va, ok ? (uint32_t)(ml * lda + 8 * kq) * 2u : kOutside);
-        } else {
-          const int kl = idx >> 4, mq = idx & 15;
-          const bool ok = m0 + 8 * mq < M && k0 + kl < ke;
-          ra[p] = ld8h(va, ok ? (uint32_t)(kl * lda + 8 * mq) * 2u : kOutside);
-        }
-        if constexpr (!BT) {
-          const int kl = idx >> 4, nq = idx & 15;
-          const bool ok = n0 + 8 * nq < N && k0 + kl < ke;
-          rb[p] = ld8h(vb, ok ? (uint32_t)(kl * ldb + 8 * nq) * 2u : kOutside);
-        } else {
-          const int nl = idx >> 2, kq = idx & 3;
-          const bool ok = n0 + nl < N && k0 + 8 * kq < ke;
-          rb[p] = ld8h(vb, ok ? (uint32_t)(nl * ldb + 8 * kq) * 2u : kOutside);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int idx = tid + 256 * e;           // element of the 128 x 32 tile
-        const int kl = idx & 31, ml = idx >> 5;  // k fastest
-        const int64_t k = k0 + kl;
-        const int64_t m = m0 + ml, n = n0 + ml;
-        sa[e] = (m < M && k < ke) ? (AT ? A[k * lda + m] : A[m * lda + k]) : (__bf16)0.0f;
-        sb[e] = (n < N && k < ke) ? (BT ? B[n * ldb + k] : B[k * ldb + n]) : (__bf16)0.0f;
-      }
-    }
-  }
-  __device__ __forceinline__ void store(__bf16 (*As)[LDS_K], __bf16 (*Bs)[LDS_K], int tid) {
-    if constexpr (VEC) {
-#pragma unroll
-      for (int p = 0; p < 2; p++) {
-        const int idx = tid + 256 * p;
-        if constexpr (!AT) {
-          const int ml = idx >> 2, kq = idx & 3;
-          *(bf16x8*)&As[ml][8 * kq] = ra[p];
-        } else {
-          const int kl = idx >> 4, mq = idx & 15;
-#pragma unroll
-          for (int e = 0; e < 8; e++) As[8 * mq + e][kl] = ra[p][e];
-        }
-        if constexpr (!BT) {
-          const int kl = idx >> 4, nq = idx & 15;
-#pragma unroll
-          for (int e = 0; e < 8; e++) Bs[8 * nq + e][kl] = rb[p][e];
-        } else {
-          const int nl = idx >> 2, kq = idx & 3;
-          *(bf16x8*)&Bs[nl][8 * kq] = rb[p];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int idx = tid + 256 * e;
-        const int kl = idx & 31, ml = idx >> 5;
-        As[ml][kl] = sa[e];
-        Bs[ml][kl] = sb[e];
-      }
-    }
-  }
-};
-
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<float> {
-  static constexpr int BK = 16;
-  // one K-step of 2 on the four 32x32 blocks of this wave
-  template <typename AS, typename BS>
-  __device__ __forceinline__ static void step(AS As, BS Bs, floatx16 (&acc)[2][2], int wm, int wn,
-                                              int lane) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const int kr = kk + (lane >> 5);
-      const float a0 = As[kr][wm * 64 + (lane & 31)];
-      const float a1 = As[kr][wm * 64 + 32 + (lane & 31)];
-      const float b0 = Bs[kr][wn * 64 + (lane & 31)];
-      const float b1 = Bs[kr][wn * 64 + 32 + (lane & 31)];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-    }
-  }
-};
-template <>
-struct Mfma<__bf16> {
-  static constexpr int BK = 32;
-  template <typename AS, typename BS>
-  __device__ __forceinline__ static void step(AS As, BS Bs, floatx16 (&acc)[2][2], int wm, int wn,
-                                              int lane) {
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 16) {
-      const int kc = kk + 8 * (lane >> 5);
-      const bf16x8 a0 = *(const bf16x8*)&As[wm * 64 + (lane & 31)][kc];
-      const bf16x8 a1 = *(const bf16x8*)&As[wm * 64 + 32 + (lane & 31)][kc];
-      const bf16x8 b0 = *(const bf16x8*)&Bs[wn * 64 + (lane & 31)][kc];
-      const bf16x8 b1 = *(const bf16x8*)&Bs[wn * 64 + 32 + (lane & 31)][kc];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1][1], 0, 0, 0);
-    }
-  }
-};
-
-// Main loop: two register stages and two LDS buffers.  The global load of
-// K-step k + 2 is issued before computing step k and stored to LDS after
-// computing step k + 1, so each load has two compute steps to arrive.  The
-// loop body is a pair of steps (an odd count gets one step of zeros).
+// Main loop: double-buffered LDS; the loads of a later step are issued before
+// a step's products and stored (split) to the other buffer after them.  FP32
+// prefetches one step ahead (a step's products take longer than a load), BF16
+// two.
 //
-// FP32: two-level accumulation.  The matrix cores accumulate each pair of
-// K-steps (32 terms) into a fresh accumulator, which is then added to the
-// running total.  A single accumulator chain over a contraction of n terms
-// carries a rounding error that grows like sqrt(n) units of FP32 rounding;
-// with chunks of c terms the chain is n / c long, which cuts the error of the
-// 800 - 10^4 term products several times.  A chunk per loop iteration keeps
-// the fresh accumulator local to the body, so it stays in the matrix-core
-// registers instead of moving through the VALU every step.
+// FP32: two-level accumulation.  Each step's 32 terms go into a fresh
+// accumulator, the small part products before the high ones, which is then
+// added to the running total: a single chain over n terms carries a rounding
+// error that grows like the square root of its length, and within a step only
+// two additions happen at the sum's full size.
 // BF16: one chain.  The inputs' rounding (2^-9 relative) dwarfs the FP32
 // chain's, and at BF16 rates the chunk additions would cost as much VALU time
 // as the products take on the matrix cores.
-template <typename T, typename St, typename TA, typename TB>
-__device__ __forceinline__ void pipeline(TA As, TB Bs, const T* __restrict__ A,
-                                         const T* __restrict__ B, int64_t lda, int64_t ldb,
-                                         int64_t M, int64_t N, int64_t Kd, int64_t m0, int64_t n0,
-                                         int64_t kb, int64_t ke, int nk, int tid,
-                                         floatx16 (&tot)[2][2], int wm, int wn, int lane) {
-  constexpr int BK = Mfma<T>::BK;
-  constexpr bool kChunked = std::is_same<T, float>::value;
-  if (nk <= 0) return;
-  St s0, s1;
-  s0.load(A, B, lda, ldb, M, N, m0, n0, kb, ke, Kd, tid);
-  s1.load(A, B, lda, ldb, M, N, m0, n0, kb + BK, ke, Kd, tid);
-  s0.store(As[0], Bs[0], tid);
-  __syncthreads();
-  auto pair = [&](int kt, floatx16(&acc)[2][2]) {
-    s0.load(A, B, lda, ldb, M, N, m0, n0, kb + (int64_t)(kt + 2) * BK, ke, Kd, tid);
-    Mfma<T>::step(As[0], Bs[0], acc, wm, wn, lane);
-    s1.store(As[1], Bs[1], tid);
-    __syncthreads();
-    s1.load(A, B, lda, ldb, M, N, m0, n0, kb + (int64_t)(kt + 3) * BK, ke, Kd, tid);
-    Mfma<T>::step(As[1], Bs[1], acc, wm, wn, lane);
-    s0.store(As[0], Bs[0], tid);
-    __syncthreads();
-  };
-  if constexpr (kChunked) {
-#pragma unroll 1
-    for (int kt = 0; kt < nk; kt += 2) {
-      floatx16 acc[2][2];
-#pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
-      pair(kt, acc);
-#pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) tot[i][j] += acc[i][j];
-    }
-  } else {
-#pragma unroll 1
-    for (int kt = 0; kt < nk; kt += 2) pair(kt, tot);
-  }
-}
-
-template <typename T, bool AT, bool BT, bool VEC>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
-  constexpr int BK = Mfma<T>::BK;
-  using St = Stage<T, AT, BT, VEC, BK>;
+template <typename T, bool AT, bool BT, bool FAR, int CFG>
+__global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) {
+  using Tl = Tile<CFG>;
+  constexpr int BM = Tl::BM, BN = Tl::BN, BI = Tl::BI, BJ = Tl::BJ, BK = bk_of<T, CFG>();
+  constexpr int NTHR = threads_of<CFG>(), NWN = BN / (32 * BJ), K8 = BK / 8, PL = parts_of<T>();
+  constexpr bool F32 = sizeof(T) == 4;
+  constexpr int NB = Tl::BUFS, DIST = F32 || NB == 1 ? 1 : 2, STEPS = 2;
+  using SA = Stage<T, AT, FAR, BM, BK, NTHR>;
+  using SB = Stage<T, !BT, FAR, BN, BK, NTHR>;
+  constexpr int RPA = SA::RP, RPB = SB::RP, ABUF = PL * K8 * RPA, BUF = ABUF + PL * K8 * RPB;
+  extern __shared__ __align__(16) unsigned char gemm_lds[];
+  uintx4* lds = (uintx4*)gemm_lds;
   // scalar copies of the argument block (keeps its address untaken)
   const T* __restrict__ A = (const T*)g.A;
   const T* __restrict__ B = (const T*)g.B;
   const int64_t M = g.M, N = g.N, Kd = g.Kd, lda = g.lda, ldb = g.ldb;
   const int splits = g.splits;
-  const int64_t kps = g.k_per_split;
-  const int sym = g.sym;
   int tx, ty, tz;
   tile_of(tx, ty, tz);
-  if (sym && ty < tx) return;  // symmetric product: upper tiles only
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
+  const int wm = w / NWN, wn = w % NWN;
   const int64_t m0 = (int64_t)tx * BM, n0 = (int64_t)ty * BN;
   int64_t kb = 0, ke = Kd;
   if (splits > 1) {
-    kb = (int64_t)tz * kps;
-    ke = kb + kps < Kd ? kb + kps : Kd;
+    kb = (int64_t)tz * g.k_per_split;
+    ke = kb + g.k_per_split < Kd ? kb + g.k_per_split : Kd;
   }
   const int nk = (int)((ke - kb + BK - 1) / BK);
-  __shared__ double red[4];
-  floatx16 acc[2][2];
+  floatx16 tot[BI][BJ];
 #pragma unroll
-  for (int i = 0; i < 2; i++)
+  for (int i = 0; i < BI; i++)
 #pragma unroll
-    for (int j = 0; j < 2; j++)
+    for (int j = 0; j < BJ; j++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
+      for (int e = 0; e < 16; e++) tot[i][j][e] = 0.0f;
 
-  if constexpr (std::is_same<T, float>::value) {
-    __shared__ float As[2][BK][St::LDS_A];
-    __shared__ float Bs[2][BK][St::LDS_B];
-    pipeline<T, St>(As, Bs, A, B, lda, ldb, M, N, Kd, m0, n0, kb, ke, nk, tid, acc, wm, wn, lane);
-  } else {
-    __shared__ __bf16 As[2][BM][St::LDS_K];
-    __shared__ __bf16 Bs[2][BN][St::LDS_K];
-    pipeline<T, St>(As, Bs, A, B, lda, ldb, M, N, Kd, m0, n0, kb, ke, nk, tid, acc, wm, wn, lane);
+  SA sa[DIST];
+  SB sb[DIST];
+#pragma unroll
+  for (int s = 0; s < DIST; s++) {
+    sa[s].init(lda, M, m0, tid);
+    sb[s].init(ldb, N, n0, tid);
   }
+  auto fetch = [&](int s, int kt) {
+    const int64_t k0 = kb + (int64_t)kt * BK;
+    sa[s].load(A, lda, M, m0, k0, ke, Kd, tid);
+    sb[s].load(B, ldb, N, n0, k0, ke, Kd, tid);
+  };
+  auto put = [&](int s, int b) {
+    sa[s].store(lds + b * BUF, tid);
+    sb[s].store(lds + b * BUF + ABUF, tid);
+  };
+  auto products = [&](int b, floatx16(&acc)[BI][BJ]) {
+    const uintx4* la = lds + b * BUF + (lane >> 5) * RPA + wm * 32 * BI + (lane & 31);
+    const uintx4* lb = lds + b * BUF + ABUF + (lane >> 5) * RPB + wn * 32 * BJ + (lane & 31);
+#pragma unroll
+    for (int s = 0; s < BK / 16; s++) {
+      bf16x8 a[PL][BI], c[PL][BJ];
+#pragma unroll
+      for (int p = PL - 1; p >= 0; p--) {
+#pragma unroll
+        for (int i = 0; i < BI; i++)
+          a[p][i] = __builtin_bit_cast(bf16x8, la[(p * K8 + 2 * s) * RPA + 32 * i]);
+#pragma unroll
+        for (int j = 0; j < BJ; j++)
+          c[p][j] = __builtin_bit_cast(bf16x8, lb[(p * K8 + 2 * s) * RPB + 32 * j]);
+      }
+      auto mul = [&](int p, int q) {
+#pragma unroll
+        for (int i = 0; i < BI; i++)
+#pragma unroll
+          for (int j = 0; j < BJ; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p][i], c[q][j], acc[i][j], 0, 0, 0);
+      };
+      if constexpr (F32) {
+        mul(2, 0);
+        mul(0, 2);
+        mul(1, 1);
+        mul(1, 0);
+        mul(0, 1);
+        // the high parts last, so that the small products are added to a sum
+        // that is still small: the last 16 terms' now, the others' below
+        if (s == BK / 16 - 1) mul(0, 0);
+      } else {
+        mul(0, 0);
+      }
+    }
+    if constexpr (F32) {
+#pragma unroll
+      for (int s = 0; s < BK / 16 - 1; s++) {
+        bf16x8 a[BI], c[BJ];
+#pragma unroll
+        for (int i = 0; i < BI; i++) a[i] = __builtin_bit_cast(bf16x8, la[2 * s * RPA + 32 * i]);
+#pragma unroll
+        for (int j = 0; j < BJ; j++) c[j] = __builtin_bit_cast(bf16x8, lb[2 * s * RPB + 32 * j]);
+#pragma unroll
+        for (int i = 0; i < BI; i++)
+#pragma unroll
+          for (int j = 0; j < BJ; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], c[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+  if (nk > 0) {
+#pragma unroll
+    for (int s = 0; s < DIST; s++)
+      if (s < nk) fetch(s, s);
+    put(0, 0);
+    __syncthreads();
+  }
+#pragma unroll 1
+  for (int kt = 0; kt < nk; kt += STEPS) {
+#pragma unroll
+    for (int u = 0; u < STEPS; u++) {
+      if (kt + u < nk) {
+        if (kt + u + DIST < nk) fetch(u % DIST, kt + u + DIST);
+        if constexpr (F32) {
+          floatx16 acc[BI][BJ];
+#pragma unroll
+          for (int i = 0; i < BI; i++)
+#pragma unroll
+            for (int j = 0; j < BJ; j++)
+#pragma unroll
+              for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
+          products(u % NB, acc);
+#pragma unroll
+          for (int i = 0; i < BI; i++)
+#pragma unroll
+            for (int j = 0; j < BJ; j++) tot[i][j] += acc[i][j];
+        } else {
+          products(u % NB, tot);
+        }
+        if (NB == 1) __syncthreads();
+        if (kt + u + 1 < nk) put((u + 1) % DIST, (u + 1) % NB);
+        __syncthreads();
+      }
+    }
+  }
+
   const bool split = splits > 1;
   float* out = split ? g.partial + (int64_t)tz * M * N : g.C;
-  epilogue(g.epi, M, N, out, split ? N : g.ldc, split, g.bias, g.D, g.ldd, g.C2, g.C, g.ldc,
-           g.red_out, acc, m0 + wm * 64, n0 + wn * 64, red,
-           sym && !split && ty != tx, g.mu_delta, (int64_t)ty * gridDim.x + tx);
+  const int64_t ldo = split ? N : g.ldc;
+  const int64_t r0 = m0 + wm * 32 * BI, c0 = n0 + wn * 32 * BJ;
+  const bool full = r0 + 32 * BI <= M && c0 + 32 * BJ <= N;
+  const float* bias = split ? nullptr : g.bias;
+  double ss = 0.0;
+#define PLNMF_EPI(E)                                                                           \
+  if constexpr (epi_used<T, AT, BT>(E)) {                                                      \
+    if (g.epi == E) {                                                                          \
+      if (full)                                                                                \
+        epi_block<E, true, BI, BJ>(M, N, out, ldo, bias, g.D, g.ldd, g.C2, g.C, g.ldc, tot, r0, \
+                                   c0, g.mu_delta, ss);                                        \
+      else                                                                                     \
+        epi_block<E, false, BI, BJ>(M, N, out, ldo, bias, g.D, g.ldd, g.C2, g.C, g.ldc, tot,    \
+                                    r0, c0, g.mu_delta, ss);                                   \
+    }                                                                                          \
+  }
+  PLNMF_EPI(EPI_STORE)
+  PLNMF_EPI(EPI_RESID_SQ)
+  PLNMF_EPI(EPI_BIAS_GELU)
+  PLNMF_EPI(EPI_BIAS_SOFTPLUS)
+  PLNMF_EPI(EPI_GELU_GRAD)
+  PLNMF_EPI(EPI_MU)
+#undef PLNMF_EPI
+  if constexpr (epi_used<T, AT, BT>(EPI_RESID_SQ)) {
+    if (g.epi == EPI_RESID_SQ) {
+      double* red = (double*)gemm_lds;  // the operand tiles are no longer read
+      for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+      if (lane == 0) red[w] = ss;
+      __syncthreads();
+      if (tid == 0) {
+        double t = 0.0;
+        for (int i = 0; i < NTHR / 64; i++) t += red[i];
+        g.red_out[(int64_t)ty * gridDim.x + tx] = t;
+      }
+    }
+  }
 }
 
 __global__ void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int64_t M,
                                      int64_t N, float* __restrict__ C, int64_t ldc,
-                                     const float* __restrict__ bias, int sym) {
+                                     const float* __restrict__ bias) {
   const int64_t total = M * N;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t m = i / N, n = i - m * N;
-    // symmetric products computed only tiles at or above the diagonal
-    const int64_t src = (sym && m / BM > n / BN) ? n * N + m : i;
     float s = 0.0f;
-    for (int z = 0; z < splits; z++) s += partial[(int64_t)z * total + src];
+    int z = 0;
+    for (; z + 3 < splits; z += 4) {  // four loads in flight, added in split order
+      const float a = partial[(int64_t)z * total + i], b = partial[(int64_t)(z + 1) * total + i];
+      const float c = partial[(int64_t)(z + 2) * total + i], d = partial[(int64_t)(z + 3) * total + i];
+      s += a;
+      s += b;
+      s += c;
+      s += d;
+    }
+    for (; z < splits; z++) s += partial[(int64_t)z * total + i];
     if (bias) s += bias[n];
     C[m * ldc + n] = s;
   }
 }
 
-bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
+
+template <typename T, bool AT, bool BT, bool FAR, int CFG>
+hipError_t launch(const GemmArgs& g, hipStream_t s) {
+  constexpr size_t bytes = lds_bytes_of<T, CFG>();
+  const void* fn = (const void*)gemm_kernel<T, AT, BT, FAR, CFG>;
+  if constexpr (bytes > 65536) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid((unsigned)((g.M + Tile<CFG>::BM - 1) / Tile<CFG>::BM),
+                  (unsigned)((g.N + Tile<CFG>::BN - 1) / Tile<CFG>::BN),
+                  (unsigned)(g.splits > 1 ? g.splits : 1));
+  gemm_kernel<T, AT, BT, FAR, CFG><<<grid, threads_of<CFG>(), bytes, s>>>(g);
+  return hipGetLastError();
+}
+
+template <typename T, bool AT, bool BT>
+hipError_t launch_form(const GemmArgs& g, bool far, int cfg, hipStream_t s) {
+  if (!epi_used<T, AT, BT>(g.epi)) return hipErrorInvalidValue;
+  if (far) return cfg == 0 ? launch<T, AT, BT, true, 0>(g, s) : launch<T, AT, BT, true, 1>(g, s);
+  switch (cfg) {
+    case 0: return launch<T, AT, BT, false, 0>(g, s);
+    case 1: return launch<T, AT, BT, false, 1>(g, s);
+    default: return launch<T, AT, BT, false, 2>(g, s);
+  }
+}
+
+template <typename T>
+hipError_t launch_elem(bool a_trans, bool b_trans, const GemmArgs& g, bool far, int cfg, hipStream_t s) {
+  if (a_trans) return b_trans ? hipErrorInvalidValue : launch_form<T, true, false>(g, far, cfg, s);
+  return b_trans ? launch_form<T, false, true>(g, far, cfg, s) : launch_form<T, false, false>(g, far, cfg, s);
+}
+
+struct CfgCost {
+  int BM, BN, bk32, bk16, occ;
+  double rate32, rate16;  // FLOP/s of one full CU
+};
+constexpr CfgCost kCfg[3] = {
+    {Tile<0>::BM, Tile<0>::BN, Tile<0>::BK32, Tile<0>::BK16, 2, 0.62e12, 2.6e12},
+    {Tile<1>::BM, Tile<1>::BN, Tile<1>::BK32, Tile<1>::BK16, 4, 0.48e12, 1.7e12},
+    {Tile<2>::BM, Tile<2>::BN, Tile<2>::BK32, Tile<2>::BK16, 2, 0.37e12, 1.3e12},
+};
 
 }  // namespace
 
-// Split-K choice: the estimated time of `s` splits is the number of rounds of
-// workgroups over the chip's slots (256 CUs, two workgroups each) times the
-// matrix-core time of one split's share of the contraction, plus the HBM time
-// of writing and summing the s partial products.  Every split keeps at least
-// 256 terms of the contraction.
-int gemm_pick_splits(int64_t M, int64_t N, int64_t Kd, int64_t* k_per_split) {
-  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  constexpr double kSlots = 512.0;
-  constexpr double kTermSec = 2.0 * BM * BN / 307.2e9;  // one term of a tile, FP32 rate per slot
-  constexpr double kBytesPerSec = 4.0e12;
-  int best = 1;
+// Tile and split-K choice: the estimated time of each is the number of rounds
+// of workgroups over the chip's slots times one split's share of the
+// contraction -- at the CU's rate shared by the workgroups on it, or at one
+// load latency per K-step where that is longer -- plus the time of writing and
+// summing the partial products.
+GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits) {
+  constexpr double kCus = 256.0, kBytesPerSec = 4.0e12;
+  constexpr double kStart = 3.0e-6, kStep = 0.6e-6, kReduce = 3.0e-6;
+  GemmPlan best{};
   double best_t = 0.0;
-  for (int s = 1; s <= 256; s++) {
-    if (s > 1 && Kd / s < 256) break;
-    int64_t kps = (Kd + s - 1) / s;
-    kps = (kps + 31) / 32 * 32;
-    const int real = (int)((Kd + kps - 1) / kps);
-    if (real != s) continue;
-    const double rounds = std::ceil((double)(tiles * s) / kSlots);
-    double t = rounds * (double)kps * kTermSec;
-    if (s > 1) t += (2.0 * s + 1.0) * (double)M * (double)N * 4.0 / kBytesPerSec;
-    if (s == 1 || t < best_t * 0.97) {  // a split must pay for itself
-      best = s;
-      best_t = t;
+  for (int c = 0; c < 3; c++) {
+    const CfgCost& f = kCfg[c];
+    const int bk = t == Elem::F32 ? f.bk32 : f.bk16;
+    const double rate = t == Elem::F32 ? f.rate32 : f.rate16;
+    const int64_t tiles = ((M + f.BM - 1) / f.BM) * ((N + f.BN - 1) / f.BN);
+    for (int s = 1; s <= max_splits; s++) {
+      if (s > 1 && Kd / s < 64) break;
+      int64_t kps = (Kd + s - 1) / s;
+      kps = (kps + 63) / 64 * 64;
+      if ((Kd + kps - 1) / kps != s) continue;
+      const double wgs = (double)tiles * s;
+      // workgroups on a CU; fewer than fit use less of its rate (one of two: 70%)
+      const double on_cu = std::min((double)f.occ, std::ceil(wgs / kCus));
+      const double share = on_cu * (1.0 + 0.9 * (f.occ - on_cu) / f.occ);
+      const double rounds = std::ceil(wgs / (kCus * f.occ));
+      const double steps = std::ceil((double)kps / bk);
+      const double step = std::max(share * 2.0 * f.BM * f.BN * bk / rate, kStep);
+      double e = rounds * (kStart + steps * step);
+      if (s > 1) e += kReduce + (2.0 * s + 1.0) * (double)M * (double)N * 4.0 / kBytesPerSec;
+      if (best_t == 0.0 || e < best_t * 0.97) {  // a change must pay for itself
+        best = GemmPlan{c, s, kps};
+        best_t = e;
+      }
     }
   }
-  int64_t kps = (Kd + best - 1) / best;
-  kps = (kps + 31) / 32 * 32;  // a multiple of both BK values
-  const int splits = (int)((Kd + kps - 1) / kps);
-  if (k_per_split) *k_per_split = kps;
-  return splits;
+  return best;
+}
+
+int gemm_tile_cols(int cfg) { return kCfg[cfg].BN; }
+
+// The residual's partial sums: one per tile of the 128 x 128 form.
+int64_t gemm_resid_tiles(int64_t M, int64_t N) {
+  return ((M + kCfg[0].BM - 1) / kCfg[0].BM) * ((N + kCfg[0].BN - 1) / kCfg[0].BN);
 }
 
 hipError_t splitk_reduce(const float* partial, int splits, int64_t M, int64_t N, float* C,
-                         int64_t ldc, const float* bias, int sym, hipStream_t s) {
+                         int64_t ldc, const float* bias, hipStream_t s) {
   const int64_t total = M * N;
   int blocks = (int)((total + 255) / 256);
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
-  splitk_reduce_kernel<<<blocks, 256, 0, s>>>(partial, splits, M, N, C, ldc, bias, sym);
+  splitk_reduce_kernel<<<blocks, 256, 0, s>>>(partial, splits, M, N, C, ldc, bias);
   return hipGetLastError();
 }
 
 hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  const int vw = t == Elem::F32 ? 4 : 8;
-  // vector path: the contiguous extent of each operand and its leading dim
-  // are multiples of the vector width, and the base is 16-byte aligned
-  const int64_t a_cont = a_trans ? g.M : g.Kd, b_cont = b_trans ? g.Kd : g.N;
-  const bool vec = aligned16(g.A) && aligned16(g.B) && g.lda % vw == 0 && g.ldb % vw == 0 &&
-                   g.lda < (int64_t(1) << 22) && g.ldb < (int64_t(1) << 22) &&
-                   a_cont % vw == 0 && b_cont % vw == 0 &&
-                   (g.splits <= 1 || g.k_per_split % vw == 0);
-  dim3 grid((unsigned)((g.M + BM - 1) / BM), (unsigned)((g.N + BN - 1) / BN),
-            (unsigned)(g.splits > 1 ? g.splits : 1));
-  const int code = (a_trans ? 4 : 0) | (b_trans ? 2 : 0) | (vec ? 1 : 0);
-#define PLNMF_GEMM_CASES(T)                                                             \
-  switch (code) {                                                                       \
-    case 0: gemm_kernel<T, false, false, false><<<grid, 256, 0, s>>>(g); break;         \
-    case 1: gemm_kernel<T, false, false, true><<<grid, 256, 0, s>>>(g); break;          \
-    case 2: gemm_kernel<T, false, true, false><<<grid, 256, 0, s>>>(g); break;          \
-    case 3: gemm_kernel<T, false, true, true><<<grid, 256, 0, s>>>(g); break;           \
-    case 4: gemm_kernel<T, true, false, false><<<grid, 256, 0, s>>>(g); break;          \
-    case 5: gemm_kernel<T, true, false, true><<<grid, 256, 0, s>>>(g); break;           \
-    case 6: gemm_kernel<T, true, true, false><<<grid, 256, 0, s>>>(g); break;           \
-    case 7: gemm_kernel<T, true, true, true><<<grid, 256, 0, s>>>(g); break;            \
-  }
-  if (t == Elem::F32) {
-    PLNMF_GEMM_CASES(float)
-  } else {
-    PLNMF_GEMM_CASES(__bf16)
-  }
-#undef PLNMF_GEMM_CASES
-  hipError_t e = hipGetLastError();
+  if (g.cfg < 0 || g.cfg > 2) return hipErrorInvalidValue;
+  if (g.epi == EPI_RESID_SQ && g.cfg != 0) return hipErrorInvalidValue;
+  // dword-aligned rows within 32-bit tile offsets; else element by element
+  const size_t es = t == Elem::F32 ? 4 : 2;
+  const bool far = !aligned(g.A, 4) || !aligned(g.B, 4) || (g.lda * es) % 4 || (g.ldb * es) % 4 ||
+                   g.lda >= (int64_t(1) << 22) || g.ldb >= (int64_t(1) << 22);
+  const hipError_t e = t == Elem::F32 ? launch_elem<float>(a_trans, b_trans, g, far, g.cfg, s)
+                                      : launch_elem<__bf16>(a_trans, b_trans, g, far, g.cfg, s);
   if (e != hipSuccess) return e;
   if (g.splits > 1 && g.epi == EPI_STORE)
-    return splitk_reduce(g.partial, g.splits, g.M, g.N, g.C, g.ldc, g.bias, g.sym, s);
+    return splitk_reduce(g.partial, g.splits, g.M, g.N, g.C, g.ldc, g.bias, s);
   return hipSuccess;
 }
 

@@ -79,19 +79,35 @@ struct GemmArgs {
   int splits;      // split-K factor (EPI_STORE only); >1 needs `partial`
   int64_t k_per_split;
   float* partial;  // [splits][M][N]
-  int sym;         // 1: C is symmetric (M == N, op(A) = op(B)^T): upper tiles, mirrored
   float mu_delta;  // EPI_MU: added to the denominator
+  int cfg;         // tile form (GemmPlan::cfg)
+};
+
+// Tile form and split-K factor of a product (see gemm_plan).
+struct GemmPlan {
+  int cfg, splits;
+  int64_t k_per_split;
 };
 
 enum class Elem { F32, BF16 };
 
-// Launch one GEMM.  Chooses tile/vector variants; returns hipError.
+// Launch one GEMM with the tile form and splits set in `g`; returns hipError.
+// EPI_RESID_SQ takes form 0 (gemm_resid_tiles partial sums).  Not both
+// operands transposed.
 hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream_t s);
-// Pick a split-K factor and return partial-buffer floats needed (0 if none).
-int gemm_pick_splits(int64_t M, int64_t N, int64_t Kd, int64_t* k_per_split);
+// Tile form and split-K factor (at most max_splits; the partial buffer holds
+// splits * M * N floats when splits > 1).
+GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits = 256);
+int gemm_tile_cols(int cfg);  // columns of C that one workgroup computes
+int64_t gemm_resid_tiles(int64_t M, int64_t N);
 // C[M,N] (ldc) = sum_z partial[z] (+ bias[n])
 hipError_t splitk_reduce(const float* partial, int splits, int64_t M, int64_t N, float* C,
-                         int64_t ldc, const float* bias, int sym, hipStream_t s);
+                         int64_t ldc, const float* bias, hipStream_t s);
+inline void gemm_use(GemmArgs& g, const GemmPlan& p) {
+  g.cfg = p.cfg;
+  g.splits = p.splits;
+  g.k_per_split = p.k_per_split;
+}
 
 // ------------------------------------------------------------------ Gram ----
 // C[K][K] (ldc) = X^T X for X [rows, K] row-major, K <= kMaxK; deterministic.
@@ -165,8 +181,11 @@ hipError_t csr_validate(int64_t rows, int64_t cols, int64_t nnz, const int32_t* 
 hipError_t normalize_columns(float* X, int64_t rows, int K, double* part, int nblk_max,
                              int32_t* flag, int bit, hipStream_t s);
 hipError_t cast_bf16(const float* x, __bf16* y, int64_t n, hipStream_t s);
-// y[c][r] = bf16(x[r][c]) for x [rows, cols]
-hipError_t cast_bf16_transpose(const float* x, __bf16* y, int64_t rows, int64_t cols,
+// y[r * ld + c] = bf16(x[r][c]) for x [rows, cols]
+hipError_t cast_bf16_rows(const float* x, __bf16* y, int64_t rows, int64_t cols, int64_t ld,
+                          hipStream_t s);
+// y[c * ld + r] = bf16(x[r][c]) for x [rows, cols]
+hipError_t cast_bf16_transpose(const float* x, __bf16* y, int64_t rows, int64_t cols, int64_t ld,
                                hipStream_t s);
 hipError_t check_finite_nonneg(const float* x, int64_t n, int32_t* flag, int bit, hipStream_t s);
 // *word |= bits, on the device, in stream order.

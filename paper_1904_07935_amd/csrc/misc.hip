@@ -62,8 +62,19 @@ __global__ void cast_kernel(const float* __restrict__ x, __bf16* __restrict__ y,
     y[i] = (__bf16)x[i];
 }
 
+// rows of the output ld apart
+__global__ void cast_rows_kernel(const float* __restrict__ x, __bf16* __restrict__ y, int64_t rows,
+                                 int64_t cols, int64_t ld) {
+  const int64_t n = rows * cols;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t r = i / cols;
+    y[r * ld + (i - r * cols)] = (__bf16)x[i];
+  }
+}
+
 __global__ void cast_t_kernel(const float* __restrict__ x, __bf16* __restrict__ y, int64_t rows,
-                              int64_t cols) {
+                              int64_t cols, int64_t ld) {
   __shared__ float tile[32][33];
   const int64_t r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 256 threads: 8 rows per pass
@@ -74,7 +85,7 @@ __global__ void cast_t_kernel(const float* __restrict__ x, __bf16* __restrict__ 
   __syncthreads();
   for (int i = ty; i < 32; i += 8) {
     const int64_t c = c0 + i, r = r0 + tx;
-    if (c < cols && r < rows) y[c * rows + r] = (__bf16)tile[tx][i];
+    if (c < cols && r < rows) y[c * ld + r] = (__bf16)tile[tx][i];
   }
 }
 
@@ -165,10 +176,16 @@ hipError_t cast_bf16(const float* x, __bf16* y, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t cast_bf16_transpose(const float* x, __bf16* y, int64_t rows, int64_t cols,
+hipError_t cast_bf16_rows(const float* x, __bf16* y, int64_t rows, int64_t cols, int64_t ld,
+                          hipStream_t s) {
+  cast_rows_kernel<<<grid_for(rows * cols), 256, 0, s>>>(x, y, rows, cols, ld);
+  return hipGetLastError();
+}
+
+hipError_t cast_bf16_transpose(const float* x, __bf16* y, int64_t rows, int64_t cols, int64_t ld,
                                hipStream_t s) {
   dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32));
-  cast_t_kernel<<<grid, 256, 0, s>>>(x, y, rows, cols);
+  cast_t_kernel<<<grid, 256, 0, s>>>(x, y, rows, cols, ld);
   return hipGetLastError();
 }
 

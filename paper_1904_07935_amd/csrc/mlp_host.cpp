@@ -69,6 +69,7 @@ struct Ws {
   float* dz1f;
   __bf16* dz1b;
   float* partial;
+  int max_splits;
   double* red;
   double* scal;
   double* csum;  // column-sum partials [kColSlices][max(K, H)]
@@ -79,11 +80,9 @@ struct Ws {
   size_t off;
 };
 
-int splits_for(int K, int H, int64_t B, int64_t* kps) {
-  const int64_t m = std::max(K, H);
-  (void)m;
-  return gemm_pick_splits(K, H, B, kps);  // the weight-gradient products are K x H and H x K
-}
+// splits of the weight-gradient products (K x H and H x K) the workspace holds:
+// it never shrinks as the batch grows, which batch_of relies on
+int splits_for(int64_t B) { return (int)std::max<int64_t>(1, std::min<int64_t>(B / 64, 16)); }
 
 Ws ws_layout(void* base, int K, int H, int64_t B) {
   Carver c(base);
@@ -97,9 +96,8 @@ Ws ws_layout(void* base, int K, int H, int64_t B) {
   w.dz2f = c.take<float>((size_t)(B * K));
   w.dz1f = c.take<float>((size_t)(B * H));
   w.dz1b = c.take<__bf16>((size_t)(B * H));
-  int64_t kps;
-  const int sp = splits_for(K, H, B, &kps);
-  w.partial = c.take<float>((size_t)std::max(sp, 1) * K * H);
+  w.max_splits = splits_for(B);
+  w.partial = c.take<float>((size_t)w.max_splits * K * H);
   w.red = c.take<double>(1024);
   w.scal = c.take<double>(8);
   w.csum = c.take<double>((size_t)kColSlices * std::max(K, H));
@@ -161,7 +159,7 @@ int forward_rows(const Params& p, int K, int H, const float* X, float* yhat, int
   g.epi = EPI_BIAS_GELU;
   g.bias = p.b1;
   g.C2 = w.gb;
-  g.splits = 1;
+  gemm_use(g, gemm_plan(Elem::BF16, g.M, g.N, g.Kd, 1));
   MLPCHECK(gemm(Elem::BF16, false, true, g, s));
   GemmArgs g2{};
   g2.A = w.gb;
@@ -176,7 +174,7 @@ int forward_rows(const Params& p, int K, int H, const float* X, float* yhat, int
   g2.epi = EPI_BIAS_SOFTPLUS;
   g2.bias = p.b2;
   g2.C2 = yhat;
-  g2.splits = 1;
+  gemm_use(g2, gemm_plan(Elem::BF16, g2.M, g2.N, g2.Kd, 1));
   MLPCHECK(gemm(Elem::BF16, false, true, g2, s));
   return NMF_OK;
 }
@@ -206,7 +204,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   a.C = gW2;
   a.ldc = H;
   a.epi = EPI_STORE;
-  a.splits = gemm_pick_splits(a.M, a.N, a.Kd, &a.k_per_split);
+  gemm_use(a, gemm_plan(Elem::BF16, a.M, a.N, a.Kd, w.max_splits));
   a.partial = w.partial;
   MLPCHECK(gemm(Elem::BF16, true, false, a, s));
   MLPCHECK(col_sum(w.dz2f, b, K, gb2, w.csum, s));
@@ -225,7 +223,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   d.D = w.z1;
   d.ldd = H;
   d.C2 = w.dz1b;
-  d.splits = 1;
+  gemm_use(d, gemm_plan(Elem::BF16, d.M, d.N, d.Kd, 1));
   MLPCHECK(gemm(Elem::BF16, false, false, d, s));
   // gW1 [H,K] = dz1^T x
   GemmArgs c{};
@@ -239,7 +237,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   c.C = gW1;
   c.ldc = K;
   c.epi = EPI_STORE;
-  c.splits = gemm_pick_splits(c.M, c.N, c.Kd, &c.k_per_split);
+  gemm_use(c, gemm_plan(Elem::BF16, c.M, c.N, c.Kd, w.max_splits));
   c.partial = w.partial;
   MLPCHECK(gemm(Elem::BF16, true, false, c, s));
   MLPCHECK(col_sum(w.dz1f, b, H, gb1, w.csum, s));
@@ -296,7 +294,7 @@ int mlp_forward_impl(const void* params, int K, int H, const float* X, float* Y,
     g.bias = p.b1;
     g.C2 = w.gb;
     g.ldc = H;
-    g.splits = 1;
+    gemm_use(g, gemm_plan(Elem::BF16, g.M, g.N, g.Kd, 1));
     MLPCHECK(gemm(Elem::BF16, false, true, g, s));
     GemmArgs g2{};
     g2.A = w.gb;
@@ -310,7 +308,7 @@ int mlp_forward_impl(const void* params, int K, int H, const float* X, float* Y,
     g2.bias = p.b2;
     g2.C2 = Y + r * K;
     g2.ldc = K;
-    g2.splits = 1;
+    gemm_use(g2, gemm_plan(Elem::BF16, g2.M, g2.N, g2.Kd, 1));
     MLPCHECK(gemm(Elem::BF16, false, true, g2, s));
   }
   return NMF_OK;

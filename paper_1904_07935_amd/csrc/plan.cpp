@@ -59,6 +59,9 @@ int tr_blocks_for(int64_t V, int64_t D, int64_t pr_floats) {
 
 namespace {
 
+// leading dimension of the BF16 copies of a dense A and of its factors' transposes
+int64_t pad8(int64_t n) { return (n + 7) / 8 * 8; }
+
 void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
   const int64_t V = s.V, D = s.D, K = s.K, nnz = s.nnz;
   const int64_t p_floats = (int64_t)(align_up((size_t)(V * K) * 4) / 4);
@@ -78,9 +81,10 @@ void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
   // split-K partials: the largest of the GEMMs a sweep launches
   size_t part = 0;
   auto need = [&](int64_t M, int64_t N, int64_t Kd) {
-    int64_t kps;
-    int sp = gemm_pick_splits(M, N, Kd, &kps);
-    if (sp > 1) part = std::max(part, (size_t)(sp * M * N));
+    for (Elem t : {Elem::F32, Elem::BF16}) {
+      const int sp = gemm_plan(t, M, N, Kd).splits;
+      if (sp > 1) part = std::max(part, (size_t)(sp * M * N));
+    }
   };
   if (s.fmt == NMF_DENSE) {
     need(D, K, V);
@@ -94,7 +98,7 @@ void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
   const size_t ph = std::max(std::max(hals_panel_floats((int)K, 16), hals_panel_floats((int)K, 32)),
                              hals_panel_floats((int)K, 64));
   float* panel_h = c.take<float>(ph);
-  const int64_t resid_tiles = ((V + 127) / 128) * ((D + 127) / 128);
+  const int64_t resid_tiles = gemm_resid_tiles(V, D);
   const int red_n = (int)std::max<int64_t>(std::max<int64_t>(resid_tiles, 1024), 1);
   double* red = c.take<double>((size_t)red_n);
   double* scal = c.take<double>(16);
@@ -171,9 +175,10 @@ void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
       p->P2 = P2;
     }
   } else if (s.prec == NMF_BF16_PRODUCTS) {
-    __bf16* Ab = c.take<__bf16>((size_t)(V * D));
-    __bf16* Atb = c.take<__bf16>((size_t)(V * D));
-    __bf16* xb = c.take<__bf16>((size_t)(std::max(V, D) * K));
+    // rows padded to 16 bytes
+    __bf16* Ab = c.take<__bf16>((size_t)(V * pad8(D)));
+    __bf16* Atb = c.take<__bf16>((size_t)(D * pad8(V)));
+    __bf16* xb = c.take<__bf16>((size_t)(std::max(pad8(V), pad8(D)) * K));
     if (p) {
       p->A_bf = Ab;
       p->At_bf = Atb;
@@ -255,6 +260,13 @@ hipError_t plnmf::gram(nmf_plan_s* p, const float* X, int64_t rows, float* out, 
 
 namespace {
 
+// Tile form and splits of a product, within the plan's partial buffer.
+void use_plan(nmf_plan_s* p, Elem t, GemmArgs& g) {
+  const int64_t cap = std::max<int64_t>(1, (int64_t)p->partial_floats / (g.M * g.N));
+  gemm_use(g, gemm_plan(t, g.M, g.N, g.Kd, (int)std::min<int64_t>(cap, 256)));
+  g.partial = p->partial;
+}
+
 // R = A^T W  (D x K)
 hipError_t product_R(nmf_plan_s* p) {
   const int K = p->K;
@@ -283,15 +295,15 @@ hipError_t product_R(nmf_plan_s* p) {
   g.C = p->R;
   g.ldc = K;
   g.epi = EPI_STORE;
-  g.splits = gemm_pick_splits(g.M, g.N, g.Kd, &g.k_per_split);
-  g.partial = p->partial;
+  use_plan(p, p->prec == NMF_BF16_PRODUCTS ? Elem::BF16 : Elem::F32, g);
   if (p->prec == NMF_BF16_PRODUCTS) {
-    hipError_t e = cast_bf16_transpose(p->W, p->X_bf, p->V, K, p->stream);  // W^T [K,V]
+    const int64_t ld = pad8(p->V);
+    hipError_t e = cast_bf16_transpose(p->W, p->X_bf, p->V, K, ld, p->stream);  // W^T [K,V]
     if (e != hipSuccess) return e;
     g.A = p->At_bf;  // [D,V]
-    g.lda = p->V;
-    g.B = p->X_bf;   // B(v,k) = WT[k*V + v]
-    g.ldb = p->V;
+    g.lda = ld;
+    g.B = p->X_bf;   // B(v,k) = WT[k*ld + v]
+    g.ldb = ld;
     return gemm(Elem::BF16, false, true, g, p->stream);
   }
   g.A = p->A_dense;  // A(d,v) = A[v*D + d]
@@ -337,8 +349,7 @@ hipError_t product_P(nmf_plan_s* p, bool force_fp32, float* out) {
     g.C = p->c_top;
     g.ldc = K;
     g.epi = EPI_STORE;
-    g.splits = gemm_pick_splits(g.M, g.N, g.Kd, &g.k_per_split);
-    g.partial = p->partial;
+    use_plan(p, bf ? Elem::BF16 : Elem::F32, g);
     e = gemm(bf ? Elem::BF16 : Elem::F32, false, false, g, p->stream);
     if (e != hipSuccess) return e;
     return scatter_rows(p->c_top, p->top_idx, p->n_top, K, out, p->stream);
@@ -350,15 +361,15 @@ hipError_t product_P(nmf_plan_s* p, bool force_fp32, float* out) {
   g.C = out;
   g.ldc = K;
   g.epi = EPI_STORE;
-  g.splits = gemm_pick_splits(g.M, g.N, g.Kd, &g.k_per_split);
-  g.partial = p->partial;
+  use_plan(p, bf ? Elem::BF16 : Elem::F32, g);
   if (bf) {
-    hipError_t e = cast_bf16_transpose(p->Ht, p->X_bf, p->D, K, p->stream);  // H [K,D]
+    const int64_t ld = pad8(p->D);
+    hipError_t e = cast_bf16_transpose(p->Ht, p->X_bf, p->D, K, ld, p->stream);  // H [K,D]
     if (e != hipSuccess) return e;
     g.A = p->A_bf;  // [V,D]
-    g.lda = p->D;
-    g.B = p->X_bf;  // B(d,k) = H[k*D + d]
-    g.ldb = p->D;
+    g.lda = ld;
+    g.B = p->X_bf;  // B(d,k) = H[k*ld + d]
+    g.ldb = ld;
     return gemm(Elem::BF16, false, true, g, p->stream);
   }
   g.A = p->A_dense;
@@ -467,9 +478,11 @@ int half_w(nmf_plan_s* p) {
 
 // Multiplicative update (the MU baseline): X <- X * N / (X G + delta) with
 // N = R, G = S (H rule, X = Ht) or N = P, G = Q (W rule, X = W).  The
-// denominator is the matrix-core product X G, whose epilogue writes the new
-// values over N (each element read, then written, by one thread: X, the
-// product's operand, is left intact); they are then copied into X.
+// denominator is the matrix-core product X G.  Its epilogue writes the new
+// values straight into X where a workgroup computes whole rows of it (K within
+// the tile's columns: it has read its rows of X by then, and no other reads
+// them), else over N (each element read, then written, by one thread), which is
+// then copied into X.
 hipError_t mu_update(nmf_plan_s* p, float* X, int64_t rows, float* N, const float* G) {
   const int K = p->K;
   GemmArgs g{};
@@ -480,16 +493,17 @@ hipError_t mu_update(nmf_plan_s* p, float* X, int64_t rows, float* N, const floa
   g.M = rows;
   g.N = K;
   g.Kd = K;
-  g.C = N;
+  gemm_use(g, gemm_plan(Elem::F32, rows, K, K, 1));
+  const bool in_place = gemm_tile_cols(g.cfg) >= K;
+  g.C = in_place ? X : N;
   g.ldc = K;
   g.epi = EPI_MU;
   g.D = N;
   g.ldd = K;
   g.C2 = X;
-  g.splits = 1;
   g.mu_delta = p->eps;
   hipError_t e = gemm(Elem::F32, false, false, g, p->stream);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || in_place) return e;
   return hipMemcpyAsync(X, N, (size_t)rows * K * sizeof(float), hipMemcpyDeviceToDevice, p->stream);
 }
 
@@ -505,7 +519,7 @@ int mu_half_w(nmf_plan_s* p) {
   TIMED(p, NMF_STEP_PRODUCT_P, product_P(p, false, p->P));
   TIMED(p, NMF_STEP_GRAM_Q, gram(p, p->Ht, p->D, p->Q));
   TIMED(p, NMF_STEP_UPDATE_W, mu_update(p, p->W, p->V, p->P, p->Q));
-  p->pq_valid = false;  // P now holds the new W
+  p->pq_valid = false;  // P may hold the new W
   return NMF_OK;
 }
 
@@ -539,9 +553,9 @@ int plnmf::enqueue_objective(nmf_plan_s* p) {
     g.ldd = p->D;
     g.red_out = p->red;
     g.splits = 1;
+    g.cfg = 0;
     HIPCHECK(p, gemm(Elem::F32, false, true, g, p->stream));
-    const int tiles = (int)(((p->V + 127) / 128) * ((p->D + 127) / 128));
-    HIPCHECK(p, finish_f64(p->red, tiles, sc + 2, p->stream));
+    HIPCHECK(p, finish_f64(p->red, (int)gemm_resid_tiles(p->V, p->D), sc + 2, p->stream));
     HIPCHECK(p, combine_objective(sc + 0, nullptr, sc + 2, sc + 3, sc + 4, p->stream));
     return NMF_OK;
   }
@@ -745,8 +759,8 @@ int nmf_init(nmf_plan* out, const nmf_matrix* A, int K, float eps, int precision
     INITCHECK(finish_f64(p->red, nb, p->scal + 0, st));
   } else {
     if (precision == NMF_BF16_PRODUCTS) {
-      INITCHECK(cast_bf16(A->dense, p->A_bf, s.V * s.D, st));
-      INITCHECK(cast_bf16_transpose(A->dense, p->At_bf, s.V, s.D, st));
+      INITCHECK(cast_bf16_rows(A->dense, p->A_bf, s.V, s.D, pad8(s.D), st));
+      INITCHECK(cast_bf16_transpose(A->dense, p->At_bf, s.V, s.D, pad8(s.V), st));
     }
     const int nb = reduce_blocks(s.V * s.D);
     INITCHECK(sumsq_f64(A->dense, s.V * s.D, p->red, nb, st));
