@@ -59,7 +59,7 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
     if (sp > 1) part = std::max(part, (size_t)sp * Dn * K);
   }
   f.partial = c.take<float>(part);
-  f.gpart = c.take<float>(gram_partial_floats(K, gram_max_chunks()));
+  f.gpart = c.take<float>(gram_partial_floats(K));
   f.panel = c.take<float>(std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),
                                     hals_panel_floats(K, 64)));
   f.red = c.take<double>(1024);
@@ -88,7 +88,7 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
 
 hipError_t gram_with(const float* X, int64_t rows, int K, float* out, float* gpart, int cus,
                      hipStream_t s, float* panel = nullptr, int tile = 32, bool rows_layout = false) {
-  return gram_xtx(X, rows, K, out, K, gpart, gram_chunks(rows, cus), s, panel, 1, tile, rows_layout);
+  return gram_xtx(X, rows, K, out, K, gpart, cus, s, panel, 1, tile, rows_layout);
 }
 
 #define FCHECK(expr)                                                                      \

@@ -35,14 +35,11 @@
 #include <cmath>
 #include <type_traits>
 
+#include "bf16x3.hpp"
 #include "internal.hpp"
 
 namespace plnmf {
 namespace {
-
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Workgroup tiles.  BM x BN outputs by waves of 32 BI x 32 BJ; BK32 / BK16 terms
 // of FP32 / BF16 operands per K-step; one LDS buffer, so that more workgroups
@@ -89,48 +86,9 @@ constexpr size_t lds_bytes_of() {
 // Operand tiles are read through buffer descriptors whose base is the step's
 // tile origin.  A lane whose element lies outside the matrix (a row past M or
 // N, a term past the end of its split) uses an offset past the descriptor's
-// range, and the hardware returns zeros for it without touching memory: no
-// branches, so the loads of a step issue back to back.  Valid offsets stay
-// below 2^31 bytes (leading dimensions of 2^22 or more, and BF16 rows that are
-// not 4-byte aligned, take the element-wise path).
-constexpr uint32_t kOutside = 0x80000000u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_view(const void* base, int64_t bytes) {
-  const int64_t n = bytes < 0 ? 0 : (bytes > 0x7fffffff ? 0x7fffffff : bytes);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, 0x00020000);
-}
-__device__ __forceinline__ uintx4 ld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-__device__ __forceinline__ unsigned ld4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
-}
-
-__device__ __forceinline__ unsigned hi_halves(unsigned lo, unsigned hi) {
-  return __builtin_amdgcn_perm(hi, lo, 0x07060302);
-}
-__device__ __forceinline__ unsigned lo_halves(unsigned lo, unsigned hi) {
-  return __builtin_amdgcn_perm(hi, lo, 0x05040100);
-}
-
-// Eight FP32 values into their three BF16 parts, packed.  The high part is the
-// value cut to BF16 (so that no finite value rounds up to infinity), the middle
-// part the rest rounded to nearest, the low part what remains (exact).
-__device__ __forceinline__ void split8(const unsigned (&x)[8], uintx4& ph, uintx4& pm, uintx4& pl) {
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    const unsigned u0 = x[2 * q], u1 = x[2 * q + 1];
-    ph[q] = hi_halves(u0, u1);
-    const floatx2 r = {__uint_as_float(u0) - __uint_as_float(u0 & 0xffff0000u),
-                       __uint_as_float(u1) - __uint_as_float(u1 & 0xffff0000u)};
-    const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
-    pm[q] = m;
-    const float l0 = r[0] - __uint_as_float(m << 16);
-    const float l1 = r[1] - __uint_as_float(m & 0xffff0000u);
-    pl[q] = hi_halves(__float_as_uint(l0), __float_as_uint(l1));
-  }
-}
-
+// range (kOutside): no branches, so the loads of a step issue back to back.
+// Valid offsets stay below 2^31 bytes (leading dimensions of 2^22 or more, and
+// BF16 rows that are not 4-byte aligned, take the element-wise path).
 __device__ __forceinline__ float gelu_grad_f(float z) {
   float cdf = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
   float pdf = expf(-0.5f * z * z) * 0.39894228040143268f;

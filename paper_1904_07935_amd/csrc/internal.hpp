@@ -111,16 +111,14 @@ inline void gemm_use(GemmArgs& g, const GemmPlan& p) {
 
 // ------------------------------------------------------------------ Gram ----
 // C[K][K] (ldc) = X^T X for X [rows, K] row-major, K <= kMaxK; deterministic.
-int gram_chunks(int64_t rows, int device_cus);  // <= gram_max_chunks()
-int gram_max_chunks();
-size_t gram_partial_floats(int K, int chunks);
+size_t gram_partial_floats(int K);  // scratch for any number of rows
 // With `panel` set, also writes the tile panels of the column updates derived
 // from C (hals_panel_floats(K) floats; entries that never depend on C -- rows
 // >= K, and outside the last tile -- must have been zeroed once), in the
 // [tile][row][column] order with the tiles' G blocks after them, or with
 // `rows_layout` in the H rows kernel's staging order (hals_h_rows_layout).
 hipError_t gram_xtx(const float* X, int64_t rows, int K, float* C, int64_t ldc, float* partial,
-                    int chunks, hipStream_t s, float* panel = nullptr, int diag_one = 0,
+                    int cus, hipStream_t s, float* panel = nullptr, int diag_one = 0,
                     int tile = 32, bool rows_layout = false);
 
 // ------------------------------------------------------------------ SpMM ----

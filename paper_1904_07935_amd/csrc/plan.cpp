@@ -92,7 +92,7 @@ void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
   }
   if (s.fmt == NMF_CSR) need(kDenseRowsMax, K, D);  // the dense rows of A in P
   float* partial = c.take<float>(std::max<size_t>(part, 1));
-  float* gpart = c.take<float>(gram_partial_floats((int)K, gram_max_chunks()));
+  float* gpart = c.take<float>(gram_partial_floats((int)K));
   float* panel = c.take<float>(hals_panel_floats((int)K));
   // the H update's panels, sized for every supported tile width
   const size_t ph = std::max(std::max(hals_panel_floats((int)K, 16), hals_panel_floats((int)K, 32)),
@@ -254,7 +254,7 @@ hipError_t plnmf::gram(nmf_plan_s* p, const float* X, int64_t rows, float* out, 
   // panel_diag 1: the H update's panels (its own buffer and tile width, in
   // the order of the kernel that will read them); 0: the W update's (32 wide)
   float* panel = panel_diag == 1 ? p->panel_h : panel_diag == 0 ? p->panel : nullptr;
-  return gram_xtx(X, rows, p->K, out, p->K, p->gram_part, gram_chunks(rows, p->cus), p->stream,
+  return gram_xtx(X, rows, p->K, out, p->K, p->gram_part, p->cus, p->stream,
                   panel, panel_diag, panel_diag == 1 ? p->h_tile : kTile, panel_diag == 1 && rows_layout);
 }
 
