@@ -239,178 +239,275 @@ __device__ __forceinline__ floatx16 block_product(const float* __restrict__ xr, 
 // ---------------------------------------------------------------- H half ----
 
 // One workgroup per 32 rows, the whole sweep of Alg. 1's H loop for them.  The
-// rows live in LDS from start to end (updated in place); per tile: the tile
+// rows live in LDS from start to end (updated in place).  Per tile: the tile
 // product on the matrix cores with the contraction split over the four waves,
-// Bterm added, then phase 2 by wave 0 (one lane per row, the tile's columns in
-// registers) while waves 1..3 stage the next tile's panel.
-// LDS (floats): xs [32][XP] | bp [kpad(K)][TP] | gt [2][T][GP] | part [3][32][TP],
-// XP = 32 * ntiles + 1 (odd: conflict-free row and column access); GP = T + 4
-// keeps every G row 16-byte aligned (phase 2 reads G rows, the same address in
-// every lane, as 16-byte vectors).
+// then waves 0 and 1 add the four shares to Bterm and run phase 2 while waves 2
+// and 3 stage the next tile's panel.
+//
+// Phase 2 is a serial chain of 32 clips, and with few rows it sets the time.
+// Four lanes (a DPP quad) share a row, lane q holding the tile's columns 4 k + q:
+// a column's value reaches the other three by a quad broadcast folded into the
+// clip, each lane updates at most eight columns per step, and the G rows come
+// from LDS, ordered by quad lane, four steps ahead.  Measured per tile at K =
+// 100 / 200 (cycles; before: one lane per row, 32 columns each, on wave 0):
+// phase 2 5,750 -> 3,050, adding the shares 1,750 -> 1,000, the product 3,200 /
+// 4,500 as before.  The whole update: 256 rows x 100 21 -> 15.5 us, 11,000 x 200
+// 46 -> 38 us, 2,741 x 77 19.5 -> 13 us.
+// LDS (floats): xs [32][XP] | bp [kpad(K)][TP] | gq [T][4][8] | part [4][32][TP],
+// XP = 32 * ntiles + 1 (odd: conflict-free row and column access).
 __host__ __device__ inline int h_xp(int K) { return 32 * ((K + T - 1) / T) + 1; }
-constexpr int GP = T + 4;
 __host__ __device__ inline size_t h_smem_floats(int K) {
-  return (size_t)kRowsH * h_xp(K) + (size_t)kpad(K) * TP + 2 * T * GP + 3 * 32 * TP;
+  return (size_t)kRowsH * h_xp(K) + (size_t)kpad(K) * TP + T * T + 4 * 32 * TP;
 }
 
-__device__ __forceinline__ void copy_panel(const float* __restrict__ panel, const float* __restrict__ gblk,
-                                           int K, int j, float* bp, float* gt, int t0, int nt) {
-  const int kp = kpad(K);
-  const floatx4* src = (const floatx4*)(panel + (int64_t)j * kp * T);
-  for (int i = t0; i < kp * T / 4; i += nt) {
-    const floatx4 v = src[i];
+// A tile's panel from global memory into the LDS by NT threads.  The loads go
+// out in batches per thread (one memory round trip each); a batch can be loaded
+// early and stored later.
+constexpr int kPanelBatch = 8;
+struct PanelBatch {
+  floatx4 v[kPanelBatch];
+};
+
+template <int NT>
+__device__ __forceinline__ void load_panel(const float* __restrict__ panel, int K, int j, int i0, int t0,
+                                           PanelBatch& pb) {
+  const int n = kpad(K) * T / 4;  // a read past the panel's view returns zeros
+  const __amdgpu_buffer_rsrc_t view = store_view((void*)(panel + (int64_t)j * n * 4), (int64_t)n * 16);
+#pragma unroll
+  for (int k = 0; k < kPanelBatch; k++)
+    pb.v[k] = __builtin_bit_cast(
+        floatx4, __builtin_amdgcn_raw_buffer_load_b128(view, (uint32_t)(i0 + t0 + NT * k) * 16, 0, 0));
+}
+
+template <int NT>
+__device__ __forceinline__ void store_panel(const PanelBatch& pb, int K, int i0, float* bp, int t0) {
+  const int n = kpad(K) * T / 4;
+#pragma unroll
+  for (int k = 0; k < kPanelBatch; k++) {
+    const int i = i0 + t0 + NT * k;
+    if (i >= n) continue;
     float* d = bp + (4 * i / T) * TP + (4 * i) % T;
-    d[0] = v[0];
-    d[1] = v[1];
-    d[2] = v[2];
-    d[3] = v[3];
+    d[0] = pb.v[k][0];
+    d[1] = pb.v[k][1];
+    d[2] = pb.v[k][2];
+    d[3] = pb.v[k][3];
   }
-  const floatx4* gs = (const floatx4*)(gblk + (int64_t)j * T * T);
-  for (int i = t0; i < T * T / 4; i += nt) *(floatx4*)(gt + (4 * i / T) * GP + (4 * i) % T) = gs[i];
+}
+
+// the batches from i0 on, loaded and stored here
+template <int NT>
+__device__ __forceinline__ void copy_panel(const float* __restrict__ panel, int K, int j, int i0, float* bp,
+                                           int t0) {
+  for (; i0 < kpad(K) * T / 4; i0 += NT * kPanelBatch) {
+    PanelBatch pb;
+    load_panel<NT>(panel, K, j, i0, t0, pb);
+    store_panel<NT>(pb, K, i0, bp, t0);
+  }
+}
+
+// Tile j's G block, two float4 per thread of 128 (row t, columns c..c+3), and its
+// place in gq[t][q][k] = G[t][4 k + q] for 4 k + q > t, else 0 (the columns that
+// step t updates).
+__device__ __forceinline__ void load_gblk(const float* __restrict__ gblk, int j, int t0, floatx4 (&g)[2]) {
+  const floatx4* src = (const floatx4*)(gblk + (int64_t)j * T * T);
+  g[0] = src[t0];
+  g[1] = src[t0 + 128];
+}
+__device__ __forceinline__ void store_gblk(const floatx4 (&g)[2], float* gq, int t0) {
+#pragma unroll
+  for (int u = 0; u < 2; u++) {
+    const int i = t0 + 128 * u, t = 4 * i / T, c = 4 * i % T;
+#pragma unroll
+    for (int e = 0; e < 4; e++) gq[(t * 4 + e) * (T / 4) + c / 4] = c + e > t ? g[u][e] : 0.0f;
+  }
+}
+
+// lane q of each group of four, in all four
+template <int Q>
+__device__ __forceinline__ float quad_bcast(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), Q * 0x55, 0xF, 0xF, true));
+}
+
+// Steps 4 G .. 4 G + 3 of phase 2 on a lane's columns y[k] = 4 k + q, with the G
+// rows g[step][k].
+template <int G>
+__device__ __forceinline__ void phase2_steps(float (&y)[T / 4], const float (&g)[4][T / 4], int q, float eps) {
+  auto step = [&](int s, float v) {
+    const float x = fmaxf(eps, v);
+    y[G] = q == s ? x : y[G];
+#pragma unroll
+    for (int k = G; k < T / 4; k++) y[k] -= x * g[s][k];  // g is 0 for columns <= t
+  };
+  step(0, quad_bcast<0>(y[G]));
+  step(1, quad_bcast<1>(y[G]));
+  step(2, quad_bcast<2>(y[G]));
+  step(3, quad_bcast<3>(y[G]));
+}
+template <int G>
+__device__ __forceinline__ void phase2_rows(float (&g)[4][T / 4], const float* gl) {
+  // only what is used (k >= G): a wider read's spare registers would be shared
+  // with the next read's, which then has to wait
+#pragma unroll
+  for (int s = 0; s < 4; s++)
+#pragma unroll
+    for (int k = G; k < T / 4; k++) g[s][k] = gl[(4 * G + s) * T + k];
+}
+// groups G.. of the tile's width tw, each group's G rows loaded during the one before
+template <int G>
+__device__ __forceinline__ void phase2(float (&y)[T / 4], float (&g)[4][T / 4], const float* gl, int q, int tw,
+                                       float eps) {
+  if constexpr (G < T / 4) {
+    if (4 * G >= tw) return;
+    float gn[4][T / 4];
+    if constexpr (G + 1 < T / 4) phase2_rows<G + 1>(gn, gl);
+    asm volatile("" ::: "memory");  // later groups' loads stay behind: registers
+    phase2_steps<G>(y, g, q, eps);
+    phase2<G + 1>(y, gn, gl, q, tw, eps);
+  }
 }
 
 template <bool VEC>
-__global__ __launch_bounds__(256) void hals_h_kernel(HalsArgs a) {
+__global__ __launch_bounds__(256, 2) void hals_h_kernel(HalsArgs a) {
   extern __shared__ float smem_raw[];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, m = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, m = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int K = a.K, kp = kpad(K), XP = h_xp(K), ntiles = (K + T - 1) / T;
   const int64_t row0 = (int64_t)blockIdx.x * kRowsH;
   const int nr = a.rows - row0 < kRowsH ? (int)(a.rows - row0) : kRowsH;
   float* xs = smem_raw;
   float* bp = xs + kRowsH * XP;
-  float* gtb = bp + kp * TP;
-  float* part = gtb + 2 * T * GP;
+  float* gq = bp + kp * TP;  // a multiple of 8 floats from the start
+  float* part = gq + T * T;
   const float eps = a.eps;
 
-  // the group's rows, zero-padded to 32 * ntiles columns
+  // the group's rows, zero-padded to 32 * ntiles columns, and the first tile's
+  // panel and G block: every load of a batch before the first store
   const int nq = 8 * ntiles;
-  for (int i = tid; i < kRowsH * nq; i += 256) {
-    const int rl = i / nq, c = 4 * (i % nq);
-    floatx4 v = floatx4{0, 0, 0, 0};
-    if (rl < nr) {
-      const float* src = a.X + (row0 + rl) * K + c;
-      if constexpr (VEC) {
-        if (c < K) v = *(const floatx4*)src;
-      } else {
+  {
+    PanelBatch first;
+    floatx4 g0[2];
+    load_panel<256>(a.panel, K, 0, 0, tid, first);
+    if (tid < 128) load_gblk(a.gblk, 0, tid, g0);
+    for (int i0 = 0; i0 < kRowsH * nq; i0 += 7 * 256) {
+      floatx4 v[7];
 #pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (c + e < K) v[e] = src[e];
+      for (int k = 0; k < 7; k++) {
+        const int i = i0 + tid + 256 * k, rl = i / nq, c = 4 * (i % nq);
+        v[k] = floatx4{0, 0, 0, 0};
+        if (rl < nr) {
+          const float* src = a.X + (row0 + rl) * K + c;
+          if constexpr (VEC) {
+            if (c < K) v[k] = *(const floatx4*)src;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              if (c + e < K) v[k][e] = src[e];
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 7; k++) {
+        const int i = i0 + tid + 256 * k, rl = i / nq, c = 4 * (i % nq);
+        if (rl >= kRowsH) continue;
+        float* d = xs + rl * XP + c;
+        d[0] = v[k][0];
+        d[1] = v[k][1];
+        d[2] = v[k][2];
+        d[3] = v[k][3];
       }
     }
-    float* d = xs + rl * XP + c;
-    d[0] = v[0];
-    d[1] = v[1];
-    d[2] = v[2];
-    d[3] = v[3];
+    store_panel<256>(first, K, 0, bp, tid);
+    if (tid < 128) store_gblk(g0, gq, tid);
+    copy_panel<256>(a.panel, K, 0, 256 * kPanelBatch, bp, tid);
   }
-  copy_panel(a.panel, a.gblk, K, 0, bp, gtb, tid, 256);
+  // phase 2: this lane's row and its columns 4 k + q of a tile
+  const int q = lane & 3, prow = 16 * w + (lane >> 2);
+  // its Bterm, loaded one tile ahead
+  // (zeros for rows past the matrix; columns past K, in the last tile, hold the
+  // next row's and are only ever written to columns that are not stored)
+  const __amdgpu_buffer_rsrc_t bview = store_view((void*)(a.Bterm + row0 * K), (int64_t)nr * K * 4);
+  auto load_bt = [&](int jt, float (&b)[T / 4]) {
+#pragma unroll
+    for (int k = 0; k < T / 4; k++)
+      b[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+          bview, (uint32_t)(prow * K + jt * T + 4 * k + q) * 4, 0, 0));
+  };
+  float btn[T / 4];
+  if (w < 2) load_bt(0, btn);
   __syncthreads();
 
   const int chunk = ((kp + 3) / 4 + 7) / 8 * 8;  // contraction per wave, a multiple of 8
   const int lb = w * chunk, le = lb + chunk < kp ? lb + chunk : kp;
-  // wave 0: a tile's Bterm in the product's lane layout, loaded one tile ahead
-  auto load_bt = [&](int jt, float (&b)[16]) {
-    const int at = jt * T, twt = at + T < K ? T : K - at;
-#pragma unroll
-    for (int jj = 0; jj < 4; jj++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int rl = 8 * jj + 4 * h + i;
-        b[4 * jj + i] = (rl < nr && m < twt) ? a.Bterm[(row0 + rl) * K + at + m] : 0.0f;
-      }
-  };
-  float btn[16];
-  if (w == 0) load_bt(0, btn);
+#pragma unroll 1
   for (int j = 0; j < ntiles; j++) {
     const int a0 = j * T, tw = a0 + T < K ? T : K - a0;
-    const float* gt = gtb + (j & 1) * T * GP;
-    float bt[16];
+    // in flight during the product: the next tile's Bterm (waves 0, 1), panel and
+    // G block (waves 2, 3)
+    float bt[T / 4];
+    PanelBatch next;
+    floatx4 gnext[2];
+    if (w < 2) {
 #pragma unroll
-    for (int e = 0; e < 16; e++) bt[e] = btn[e];
-    if (w == 0 && j + 1 < ntiles) load_bt(j + 1, btn);
-    // the tile product, contraction [lb, le) of this wave
+      for (int k = 0; k < T / 4; k++) bt[k] = btn[k];
+      if (j + 1 < ntiles) load_bt(j + 1, btn);
+    } else if (j + 1 < ntiles) {
+      load_panel<128>(a.panel, K, j + 1, 0, tid - 128, next);
+      load_gblk(a.gblk, j + 1, tid - 128, gnext);
+    }
+    // the tile product, contraction [lb, le) of this wave; each step's operands
+    // are read during the step before
     floatx16 acc;
 #pragma unroll
     for (int e = 0; e < 16; e++) acc[e] = 0.0f;
-    for (int l = lb; l < le; l += 8) {
+    if (lb < le) {
+      float xv[4], bv[4];
+      auto read = [&](int l) {
 #pragma unroll
-      for (int s = 0; s < 4; s++) {
-        const int ll = l + 2 * s + h;
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[m * XP + ll], bp[ll * TP + m], acc, 0, 0, 0);
+        for (int s = 0; s < 4; s++) {
+          xv[s] = xs[m * XP + l + 2 * s + h];
+          bv[s] = bp[(l + 2 * s + h) * TP + m];
+        }
+      };
+      read(lb);
+      for (int l = lb; l < le; l += 8) {
+        float xc[4], bc[4];
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+          xc[s] = xv[s];
+          bc[s] = bv[s];
+        }
+        if (l + 8 < le) read(l + 8);
+#pragma unroll
+        for (int s = 0; s < 4; s++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xc[s], bc[s], acc, 0, 0, 0);
       }
     }
-    if (w > 0) {
-      float* pw = part + (w - 1) * 32 * TP;
+    float* pw = part + w * 32 * TP;
 #pragma unroll
-      for (int jj = 0; jj < 4; jj++)
+    for (int jj = 0; jj < 4; jj++)
 #pragma unroll
-        for (int i = 0; i < 4; i++) pw[(8 * jj + 4 * h + i) * TP + m] = acc[4 * jj + i];
-    }
+      for (int i = 0; i < 4; i++) pw[(8 * jj + 4 * h + i) * TP + m] = acc[4 * jj + i];
     __syncthreads();
-    if (w == 0) {
-      // y = Bterm + product, into part[0] (each element read, then written, by one lane)
+    if (w < 2) {
+      float g[4][T / 4];
+      phase2_rows<0>(g, gq + q * (T / 4));
+      // y = Bterm + product
+      float y[T / 4];
+      const float* p = part + prow * TP + q;
 #pragma unroll
-      for (int jj = 0; jj < 4; jj++)
+      for (int k = 0; k < T / 4; k++)
+        y[k] = bt[k] + ((p[4 * k] + p[32 * TP + 4 * k]) + p[64 * TP + 4 * k]) + p[96 * TP + 4 * k];
+      phase2<0>(y, g, gq + q * (T / 4), q, tw, eps);
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const int e = (8 * jj + 4 * h + i) * TP + m;
-          part[e] = bt[4 * jj + i] + ((acc[4 * jj + i] + part[e]) + part[32 * TP + e]) + part[64 * TP + e];
-        }
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      // phase 2: one lane per row, the tile's columns in registers
-      if (lane < kRowsH) {
-        float y[T];
-#pragma unroll
-        for (int c = 0; c < T; c++) y[c] = part[lane * TP + c];
-        if (tw == T) {
-          // a full tile: no branch per step (a branch around a step makes the
-          // compiler copy all of y on both sides of it), and step t + 1's G row
-          // loaded during step t; the compiler barrier keeps later rows' loads
-          // from being hoisted further, which would exhaust the registers
-          float gr[T];
-#pragma unroll
-          for (int q = 0; q < T / 4; q++) {
-            const floatx4 v = *(const floatx4*)(gt + 4 * q);
-#pragma unroll
-            for (int e = 0; e < 4; e++) gr[4 * q + e] = v[e];
-          }
-#pragma unroll
-          for (int t = 0; t < T; t++) {
-            float gn[T];
-#pragma unroll
-            for (int q = (t + 2) / 4; q < T / 4; q++) {
-              const floatx4 v = *(const floatx4*)(gt + (t + 1) * GP + 4 * q);
-#pragma unroll
-              for (int e = 0; e < 4; e++) gn[4 * q + e] = v[e];
-            }
-            asm volatile("" ::: "memory");
-            const float x = fmaxf(eps, y[t]);
-            y[t] = x;
-#pragma unroll
-            for (int c = t + 1; c < T; c++) y[c] -= x * gr[c];
-#pragma unroll
-            for (int c = t + 2; c < T; c++) gr[c] = gn[c];
-          }
-        } else {
-#pragma unroll
-          for (int t = 0; t < T; t++) {
-            if (t < tw) {
-              const float x = fmaxf(eps, y[t]);
-              y[t] = x;
-#pragma unroll
-              for (int c = t + 1; c < T; c++) y[c] -= x * gt[t * GP + c];
-            }
-          }
-        }
-#pragma unroll
-        for (int c = 0; c < T; c++)
-          if (c < tw) xs[lane * XP + a0 + c] = y[c];
-      }
+      for (int k = 0; k < T / 4; k++)
+        if (4 * k + q < tw) xs[prow * XP + a0 + 4 * k + q] = y[k];
     } else if (j + 1 < ntiles) {
-      // waves 1..3: the next tile's panel (bp is free once every wave has its product)
-      copy_panel(a.panel, a.gblk, K, j + 1, bp, gtb + ((j + 1) & 1) * T * GP, tid - 64, 192);
+      // the next tile's panel (bp is free once every wave has its product)
+      store_panel<128>(next, K, 0, bp, tid - 128);
+      copy_panel<128>(a.panel, K, j + 1, 128 * kPanelBatch, bp, tid - 128);
     }
     __syncthreads();
+    // the next G block, read again only after the next product's barrier
+    if (w >= 2 && j + 1 < ntiles) store_gblk(gnext, gq, tid - 128);
   }
   // the finished rows back to X
   for (int i = tid; i < kRowsH * nq; i += 256) {
@@ -1321,7 +1418,7 @@ int hals_rows_per_group_h() { return kRowsH; }
 // LDS-resident kernel (32 rows per workgroup) keeps more CUs busy, as long as
 // all its workgroups are resident at once; once they need a second round (its
 // LDS holds two workgroups per CU up to K = 224, one above), the rows kernel's
-// single round is shorter.  Measured on 11,000 rows: K = 200 LDS 48 us, rows
+// single round is shorter.  Measured on 11,000 rows: K = 200 LDS 38 us, rows
 // 64 us; K = 240 LDS 96 us, rows 76 us; K = 400 LDS 220 us, rows 161 us; on
 // 10,000 rows at K = 240: LDS 111 us, rows 79 us.
 // NMF_H_KERNEL=rows|lds forces one (read when the half starts: measurement,
@@ -1332,7 +1429,9 @@ static bool h_rows_kernel_for(int64_t rows, int K, int cus) {
     if (e[0] == 'l') return false;
   }
   if (rows >= 32768) return true;
-  const int64_t per_cu = (int64_t)(kRrLdsMax / (h_smem_floats(K) * 4));
+  // the LDS kernel's workgroups per CU, by 5,472 floats beside its rows and panel
+  const size_t floats = (size_t)kRowsH * h_xp(K) + (size_t)kpad(K) * TP + 5472;
+  const int64_t per_cu = (int64_t)(kRrLdsMax / (floats * 4));
   const int64_t groups = (rows + kRowsH - 1) / kRowsH;
   return groups > (int64_t)(cus > 0 ? cus : 256) * per_cu;
 }
