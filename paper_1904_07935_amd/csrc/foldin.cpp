@@ -31,13 +31,13 @@ struct FoldWs {
   float* gpart;   // Gram partials
   float* panel;   // tile panels of the H update
   double* red;
-  double* scal;   // [0] a2 [1] wp [2] sq [3] half [4] rel
+  double* scal;   // [0] a2 [3] half [4] rel, then the counters
   double* trace;  // [kTraceChunk]
   int4* items;
   int32_t* item_slot;
   int32_t* fix;
   float* carry;
-  int32_t* counter;
+  int32_t* counter;  // [0] objective blocks [1] check flags [2] segments [3] long rows
   float* xn;      // MLP input [D',K]
   float* norms;   // [D']
   float* y;       // MLP output [D',K]
@@ -62,8 +62,9 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
   f.gpart = c.take<float>(gram_partial_floats(K));
   f.panel = c.take<float>(std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),
                                     hals_panel_floats(K, 64)));
-  f.red = c.take<double>(1024);
-  f.scal = c.take<double>(8);
+  f.red = c.take<double>(kObjParts);
+  f.scal = c.take<double>(8 + 2);
+  f.counter = (int32_t*)(f.scal + 8);
   f.trace = c.take<double>(kTraceChunk);
   if (AnewT->format == NMF_CSR) {
     f.L = spmm_item_nnz(AnewT->nnz);
@@ -72,7 +73,6 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
     f.item_slot = c.take<int32_t>((size_t)z.items);
     f.fix = c.take<int32_t>((size_t)(3 * z.fix));
     f.carry = c.take<float>((size_t)(z.seg * K));
-    f.counter = c.take<int32_t>(4);
   }
   if (hidden > 0) {
     f.xn = c.take<float>((size_t)(Dn * K));
@@ -101,13 +101,8 @@ int fold_objective(nmf_plan_s* p, const FoldWs& f, float* Ht, int64_t Dn, double
                    hipStream_t s) {
   const int K = p->K;
   FCHECK(gram_with(Ht, Dn, K, f.Qn, f.gpart, p->cus, s));
-  int nb = reduce_blocks(Dn * K);
-  FCHECK(dot_f64(Ht, f.R, Dn * K, f.red, nb, s));
-  FCHECK(finish_f64(f.red, nb, f.scal + 1, s));
-  nb = reduce_blocks((int64_t)K * K);
-  FCHECK(dot_f64(f.S, f.Qn, (int64_t)K * K, f.red, nb, s));
-  FCHECK(finish_f64(f.red, nb, f.scal + 2, s));
-  FCHECK(combine_objective(f.scal + 0, f.scal + 1, f.scal + 2, f.scal + 3, dst, s));
+  FCHECK(objective_identity(f.scal + 0, Ht, f.R, Dn * K, f.S, f.Qn, (int64_t)K * K, f.red, f.counter + 0,
+                            f.scal + 3, dst, s));
   return NMF_OK;
 }
 
@@ -170,12 +165,15 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
     return fail(NMF_E_WORKSPACE, "fold-in workspace %zu < %zu", workspace_bytes, f.off);
   hipStream_t s = p->stream;
 
-  // validate and build the product plan for the new documents
-  FCHECK(hipMemsetAsync(f.scal, 0, 8 * sizeof(double), s));
+  // ||A_new||^2 only where an objective is asked for
+  const bool objective = rel_trace || tol > 0.0;
+  // validate the new documents, plan their long rows and form R'
+  FCHECK(hipMemsetAsync(f.scal, 0, 10 * sizeof(double), s));  // with the counters
   if (AnewT->format == NMF_CSR) {
-    FCHECK(hipMemsetAsync(f.counter, 0, 4 * sizeof(int32_t), s));
+    const SpmmSizes z = spmm_sizes(Dn, AnewT->nnz, f.L);
+    const CsrSegments seg{f.items, f.item_slot, f.fix, f.counter + 2, z.seg, z.fix, f.L};
     FCHECK(csr_validate(Dn, p->V, AnewT->nnz, AnewT->rowptr, AnewT->colidx, AnewT->values,
-                        f.counter + 1, s));
+                        f.counter + 1, s, seg));
     int32_t flag = 0;
     FCHECK(hipMemcpyAsync(&flag, f.counter + 1, sizeof(flag), hipMemcpyDeviceToHost, s));
     FCHECK(hipStreamSynchronize(s));
@@ -192,11 +190,12 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
     sp.item_slot = f.item_slot;
     sp.fix = f.fix;
     sp.carry = f.carry;
-    FCHECK(spmm_build(&sp, s));
-    FCHECK(spmm(sp, Elem::F32, p->W, K, f.R, s));
-    const int nb = reduce_blocks(AnewT->nnz);
-    FCHECK(sumsq_f64(AnewT->values, AnewT->nnz, f.red, nb, s));
-    FCHECK(finish_f64(f.red, nb, f.scal + 0, s));
+    FCHECK(spmm_unplanned(sp, f.counter + 2, p->W, K, f.R, s));
+    if (objective) {
+      const int nb = reduce_blocks(AnewT->nnz);
+      FCHECK(sumsq_f64(AnewT->values, AnewT->nnz, f.red, nb, s));
+      FCHECK(finish_f64(f.red, nb, f.scal + 0, s));
+    }
   } else {
     GemmArgs g{};
     g.A = AnewT->dense;
@@ -212,9 +211,11 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
     gemm_use(g, gemm_plan(Elem::F32, g.M, g.N, g.Kd));
     g.partial = f.partial;
     FCHECK(gemm(Elem::F32, false, false, g, s));
-    const int nb = reduce_blocks(Dn * p->V);
-    FCHECK(sumsq_f64(AnewT->dense, Dn * p->V, f.red, nb, s));
-    FCHECK(finish_f64(f.red, nb, f.scal + 0, s));
+    if (objective) {
+      const int nb = reduce_blocks(Dn * p->V);
+      FCHECK(sumsq_f64(AnewT->dense, Dn * p->V, f.red, nb, s));
+      FCHECK(finish_f64(f.red, nb, f.scal + 0, s));
+    }
   }
   FCHECK(hipMemsetAsync(f.panel, 0,
                         std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),

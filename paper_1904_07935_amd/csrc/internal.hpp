@@ -158,6 +158,10 @@ hipError_t csr_dense_rows(const int32_t* rowptr, const int32_t* col, const float
 hipError_t scatter_rows(const float* src, const int32_t* rows, int n, int K, float* dst,
                         hipStream_t s);
 hipError_t spmm(const SpmmPlan& p, Elem t, const void* X, int K, float* out, hipStream_t s);
+// out = matrix * X without a host plan: p.items, item_slot, fix and `counts` as
+// csr_validate leaves them.  Same sums as spmm.
+hipError_t spmm_unplanned(const SpmmPlan& p, const int32_t* counts, const float* X, int K, float* out,
+                          hipStream_t s);
 // Columns [k0, k0 + K) only: out[r, k0 + c] = sum_j a[r, j] X[col_j, k0 + c],
 // X rows ldx apart, out rows ldo apart.
 hipError_t spmm_slice(const SpmmPlan& p, Elem t, const void* X, int64_t ldx, int k0, int K,
@@ -170,8 +174,19 @@ hipError_t csr_transpose(int64_t rows, int64_t cols, int64_t nnz, const int32_t*
                          const int32_t* col, const float* val, int32_t* t_rowptr, int32_t* t_col,
                          float* t_val, int32_t* scratch, int nblk, hipStream_t s);
 // Structure check: sets flag bits (1 rowptr, 2 col range/order, 4 value) in *flag.
+// With `seg.items` set, also plans the segments of rows longer than L for
+// spmm_unplanned (arrays sized by spmm_sizes; counts zeroed by the caller).
+struct CsrSegments {
+  int4* items;
+  int32_t* slot;
+  int32_t* fix;
+  int32_t* counts;  // [0] segments, [1] long rows
+  int64_t max_seg, max_fix;
+  int L;
+};
 hipError_t csr_validate(int64_t rows, int64_t cols, int64_t nnz, const int32_t* rowptr,
-                        const int32_t* col, const float* val, int32_t* flag, hipStream_t s);
+                        const int32_t* col, const float* val, int32_t* flag, hipStream_t s,
+                        const CsrSegments& seg = CsrSegments{});
 
 // ----------------------------------------------------------- elementwise ----
 // Scales every column of X [rows, K] to unit L2 norm; a column of zero norm
@@ -192,12 +207,17 @@ hipError_t or_bits(int32_t* word, int32_t bits, hipStream_t s);
 // FP64 fixed-order reductions.  partial buffers are [nblk] doubles.
 int reduce_blocks(int64_t n);
 hipError_t sumsq_f64(const float* x, int64_t n, double* partial, int nblk, hipStream_t s);
-hipError_t dot_f64(const float* x, const float* y, int64_t n, double* partial, int nblk,
-                   hipStream_t s);
 hipError_t finish_f64(const double* partial, int n, double* out, hipStream_t s);
-// out[0] = a2 + c1 * x[0] + c2 * y[0] ... combine for the sparse identity
-hipError_t combine_objective(const double* a2, const double* wp, const double* sq,
-                             double* out_half, double* out_rel, hipStream_t s);
+// The objective by the identity e2 = a2 - 2 <x, y> + <g, q> in one launch: out_half
+// = e2 / 2, out_rel = sqrt(e2 / a2).  part: kObjParts doubles, count: a zeroed word
+// (left zeroed).
+constexpr int kObjParts = 1024;
+hipError_t objective_identity(const double* a2, const float* x, const float* y, int64_t n1, const float* g,
+                              const float* q, int64_t n2, double* part, int32_t* count, double* out_half,
+                              double* out_rel, hipStream_t s);
+// the same from an explicit residual e2
+hipError_t combine_objective(const double* a2, const double* e2, double* out_half, double* out_rel,
+                             hipStream_t s);
 
 // --------------------------------------------------------- HALS updates ----
 // One tiled half-sweep over the rows of X [rows, K] (in place):

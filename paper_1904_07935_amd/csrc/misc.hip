@@ -2,6 +2,8 @@
 // of W before the first sweep, BF16 operand casts, input checks, and the
 // fixed-order FP64 reductions of the objective (Eq. 2 and the relative
 // objective of Sec. 6.2).
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace plnmf {
@@ -111,18 +113,6 @@ __global__ void sumsq_kernel(const float* __restrict__ x, int64_t n, double* __r
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-// sum of x*y over FP32 inputs, products and sums in FP64
-__global__ void dot_kernel(const float* __restrict__ x, const float* __restrict__ y, int64_t n,
-                           double* __restrict__ part) {
-  __shared__ double sh[16];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    s += (double)x[i] * (double)y[i];
-  const double t = block_sum_d(s, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-
 __global__ void finish_kernel(const double* __restrict__ part, int n, double* __restrict__ out) {
   __shared__ double sh[16];
   double s = 0.0;
@@ -132,14 +122,67 @@ __global__ void finish_kernel(const double* __restrict__ part, int n, double* __
   if (threadIdx.x == 0) out[0] = t;
 }
 
-// out_half = e2 / 2, out_rel = sqrt(e2 / a2) with e2 = a2 - 2 wp + sq (identity)
-// or e2 = sq when wp is null (explicit residual)
-__global__ void combine_kernel(const double* a2, const double* wp, const double* sq,
-                               double* out_half, double* out_rel) {
-  double e2 = wp ? a2[0] - 2.0 * wp[0] + sq[0] : sq[0];
+__device__ __forceinline__ void put_objective(double a2, double e2, double* out_half, double* out_rel) {
   if (e2 < 0.0) e2 = 0.0;
   out_half[0] = 0.5 * e2;
-  out_rel[0] = sqrt(e2 / a2[0]);
+  out_rel[0] = sqrt(e2 / a2);
+}
+
+__global__ void combine_kernel(const double* a2, const double* e2, double* out_half, double* out_rel) {
+  put_objective(a2[0], e2[0], out_half, out_rel);
+}
+
+// Two dot products over FP32 inputs, products and sums in FP64, and what is made
+// of them, in one launch (five before: at a few hundred rows each took longer
+// to start than to run: 17 -> 6 us at 256 x 100).  Blocks [0, nb1) take x y, the rest g q, a fixed
+// share each; the last block to finish adds the partial sums in block order, so
+// the result does not depend on which one that is.
+__global__ __launch_bounds__(256) void objective_kernel(const double* __restrict__ a2,
+                                                        const float* __restrict__ x,
+                                                        const float* __restrict__ y, int64_t n1,
+                                                        const float* __restrict__ g,
+                                                        const float* __restrict__ q, int64_t n2, int nb1,
+                                                        double* part, int32_t* count, double* out_half,
+                                                        double* out_rel) {
+  __shared__ double sh[16];
+  __shared__ int last;
+  const bool first = (int)blockIdx.x < nb1;
+  const float* __restrict__ u = first ? x : g;
+  const float* __restrict__ v = first ? y : q;
+  const int64_t n = first ? n1 : n2;
+  const int64_t b = first ? blockIdx.x : blockIdx.x - nb1, nb = first ? nb1 : gridDim.x - nb1;
+  double s = 0.0;
+  const int64_t st = nb * 256;
+  int64_t i = b * 256 + threadIdx.x;
+  for (; i + 3 * st < n; i += 4 * st) {  // four loads of each in flight
+    const float u0 = u[i], u1 = u[i + st], u2 = u[i + 2 * st], u3 = u[i + 3 * st];
+    const float v0 = v[i], v1 = v[i + st], v2 = v[i + 2 * st], v3 = v[i + 3 * st];
+    s += (double)u0 * (double)v0;
+    s += (double)u1 * (double)v1;
+    s += (double)u2 * (double)v2;
+    s += (double)u3 * (double)v3;
+  }
+  for (; i < n; i += st) s += (double)u[i] * (double)v[i];
+  const double t = block_sum_d(s, sh);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(part + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(count, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+           (int)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  double d1 = 0.0, d2 = 0.0;
+  for (int k = threadIdx.x; k < (int)gridDim.x; k += 256) {
+    const double p = __hip_atomic_load(part + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (k < nb1) d1 += p;
+    else d2 += p;
+  }
+  d1 = block_sum_d(d1, sh);
+  d2 = block_sum_d(d2, sh);
+  if (threadIdx.x == 0) {
+    put_objective(a2[0], a2[0] - 2.0 * d1 + d2, out_half, out_rel);
+    *count = 0;
+  }
 }
 
 }  // namespace
@@ -206,23 +249,27 @@ hipError_t sumsq_f64(const float* x, int64_t n, double* partial, int nblk, hipSt
   return hipGetLastError();
 }
 
-hipError_t dot_f64(const float* x, const float* y, int64_t n, double* partial, int nblk,
-                   hipStream_t s) {
-  dot_kernel<<<nblk, 256, 0, s>>>(x, y, n, partial);
-  return hipGetLastError();
-}
-
 hipError_t finish_f64(const double* partial, int n, double* out, hipStream_t s) {
   finish_kernel<<<1, 256, 0, s>>>(partial, n, out);
   return hipGetLastError();
 }
 
-hipError_t combine_objective(const double* a2, const double* wp, const double* sq,
-                             double* out_half, double* out_rel, hipStream_t s) {
-  combine_kernel<<<1, 1, 0, s>>>(a2, wp, sq, out_half, out_rel);
+hipError_t combine_objective(const double* a2, const double* e2, double* out_half, double* out_rel,
+                             hipStream_t s) {
+  combine_kernel<<<1, 1, 0, s>>>(a2, e2, out_half, out_rel);
   return hipGetLastError();
 }
 
+hipError_t objective_identity(const double* a2, const float* x, const float* y, int64_t n1, const float* g,
+                              const float* q, int64_t n2, double* part, int32_t* count, double* out_half,
+                              double* out_rel, hipStream_t s) {
+  // about 2,048 products per block
+  const int nb1 = (int)std::max<int64_t>(1, std::min<int64_t>((n1 + 2047) / 2048, kObjParts - 128));
+  const int nb2 = (int)std::max<int64_t>(1, std::min<int64_t>((n2 + 2047) / 2048, 128));
+  objective_kernel<<<(unsigned)(nb1 + nb2), 256, 0, s>>>(a2, x, y, n1, g, q, n2, nb1, part, count, out_half,
+                                                      out_rel);
+  return hipGetLastError();
+}
 
 namespace {
 __global__ void dense_rows_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,

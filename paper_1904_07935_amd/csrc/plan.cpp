@@ -99,7 +99,7 @@ void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
                              hals_panel_floats((int)K, 64));
   float* panel_h = c.take<float>(ph);
   const int64_t resid_tiles = gemm_resid_tiles(V, D);
-  const int red_n = (int)std::max<int64_t>(std::max<int64_t>(resid_tiles, 1024), 1);
+  const int red_n = (int)std::max<int64_t>(resid_tiles, kObjParts);
   double* red = c.take<double>((size_t)red_n);
   double* scal = c.take<double>(16);
   unsigned long long* slots = c.take<unsigned long long>(kSlotWords);
@@ -107,7 +107,7 @@ void layout(const ShapeInfo& s, Carver& c, nmf_plan_s* p) {
   const int64_t wtiles = (K + kTile - 1) / kTile;
   float* whand = c.take<float>((size_t)(wtiles * V * kTile));
   float* wnew = c.take<float>((size_t)(wtiles * V * kTile));
-  int32_t* status = c.take<int32_t>(16);
+  int32_t* status = c.take<int32_t>(16);  // [8]: the objective's block count
   double* colsq = c.take<double>((size_t)1024 * K);
   if (p) {
     p->colsq = colsq;
@@ -556,7 +556,7 @@ int plnmf::enqueue_objective(nmf_plan_s* p) {
     g.cfg = 0;
     HIPCHECK(p, gemm(Elem::F32, false, true, g, p->stream));
     HIPCHECK(p, finish_f64(p->red, (int)gemm_resid_tiles(p->V, p->D), sc + 2, p->stream));
-    HIPCHECK(p, combine_objective(sc + 0, nullptr, sc + 2, sc + 3, sc + 4, p->stream));
+    HIPCHECK(p, combine_objective(sc + 0, sc + 2, sc + 3, sc + 4, p->stream));
     return NMF_OK;
   }
   float* Puse = p->P;
@@ -566,15 +566,8 @@ int plnmf::enqueue_objective(nmf_plan_s* p) {
     HIPCHECK(p, gram(p, p->Ht, p->D, p->Q));
   }
   HIPCHECK(p, gram(p, p->W, p->V, p->S2));
-  const int64_t n1 = p->V * p->K;
-  int nb = reduce_blocks(n1);
-  HIPCHECK(p, dot_f64(p->W, Puse, n1, p->red, nb, p->stream));
-  HIPCHECK(p, finish_f64(p->red, nb, sc + 1, p->stream));
-  const int64_t n2 = (int64_t)p->K * p->K;
-  nb = reduce_blocks(n2);
-  HIPCHECK(p, dot_f64(p->S2, p->Q, n2, p->red, nb, p->stream));
-  HIPCHECK(p, finish_f64(p->red, nb, sc + 2, p->stream));
-  HIPCHECK(p, combine_objective(sc + 0, sc + 1, sc + 2, sc + 3, sc + 4, p->stream));
+  HIPCHECK(p, objective_identity(sc + 0, p->W, Puse, p->V * p->K, p->S2, p->Q, (int64_t)p->K * p->K, p->red,
+                                 p->status + 8, sc + 3, sc + 4, p->stream));
   return NMF_OK;
 }
 
