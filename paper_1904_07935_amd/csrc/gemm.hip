@@ -252,7 +252,8 @@ __device__ __forceinline__ void epi_block(int64_t M, int64_t N, float* __restric
                                           int64_t ldo, const float* __restrict__ bs,
                                           const float* Dm, int64_t ldd, void* C2, float* C,
                                           int64_t ldc, floatx16 (&acc)[BI][BJ], int64_t r0,
-                                          int64_t c0, float mu_delta, double& ss) {
+                                          int64_t c0, float mu_delta, float scale, double& ss,
+                                          double (&cs)[BJ]) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < BI; i++)
@@ -281,8 +282,16 @@ __device__ __forceinline__ void epi_block(int64_t M, int64_t N, float* __restric
             ((float*)C2)[m * ldc + n] = softplus_f(z);
           } else if constexpr (EPI == EPI_GELU_GRAD) {
             const float d = v * gelu_grad_f(Dm[m * ldd + n]);
-            if (C) C[m * ldc + n] = d;
             ((__bf16*)C2)[m * ldc + n] = (__bf16)d;
+            cs[j] += (double)d;
+          } else if constexpr (EPI == EPI_OUT_GRAD) {
+            const float z = v + bs[n];
+            const float e = softplus_f(z) - Dm[m * ldd + n];
+            ss += (double)e * (double)e;
+            const float sg = z > 20.0f ? 1.0f : 1.0f / (1.0f + expf(-z));
+            const float d = scale * e * sg;
+            ((__bf16*)C2)[m * ldc + n] = (__bf16)d;
+            cs[j] += (double)d;
           } else if constexpr (EPI == EPI_MU) {
             const float num = Dm[m * ldd + n], x = ((const float*)C2)[m * ldc + n];
             C[m * ldc + n] = x * num / (v + mu_delta);
@@ -295,7 +304,7 @@ template <typename T, bool AT, bool BT>
 __host__ __device__ constexpr bool epi_used(int epi) {
   if (epi == EPI_STORE) return true;
   if (sizeof(T) == 4) return (epi == EPI_MU && !AT && !BT) || (epi == EPI_RESID_SQ && !AT && BT);
-  if (!AT && BT) return epi == EPI_BIAS_GELU || epi == EPI_BIAS_SOFTPLUS;
+  if (!AT && BT) return epi == EPI_BIAS_GELU || epi == EPI_BIAS_SOFTPLUS || epi == EPI_OUT_GRAD;
   return epi == EPI_GELU_GRAD && !AT && !BT;
 }
 
@@ -473,16 +482,18 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
   const int64_t r0 = m0 + wm * 32 * BI, c0 = n0 + wn * 32 * BJ;
   const bool full = r0 + 32 * BI <= M && c0 + 32 * BJ <= N;
   const float* bias = split ? nullptr : g.bias;
-  double ss = 0.0;
+  double ss = 0.0, cs[BJ];
+#pragma unroll
+  for (int j = 0; j < BJ; j++) cs[j] = 0.0;
 #define PLNMF_EPI(E)                                                                           \
   if constexpr (epi_used<T, AT, BT>(E)) {                                                      \
     if (g.epi == E) {                                                                          \
       if (full)                                                                                \
         epi_block<E, true, BI, BJ>(M, N, out, ldo, bias, g.D, g.ldd, g.C2, g.C, g.ldc, tot, r0, \
-                                   c0, g.mu_delta, ss);                                        \
+                                   c0, g.mu_delta, g.scale, ss, cs);                           \
       else                                                                                     \
         epi_block<E, false, BI, BJ>(M, N, out, ldo, bias, g.D, g.ldd, g.C2, g.C, g.ldc, tot,    \
-                                    r0, c0, g.mu_delta, ss);                                   \
+                                    r0, c0, g.mu_delta, g.scale, ss, cs);                      \
     }                                                                                          \
   }
   PLNMF_EPI(EPI_STORE)
@@ -491,10 +502,13 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
   PLNMF_EPI(EPI_BIAS_SOFTPLUS)
   PLNMF_EPI(EPI_GELU_GRAD)
   PLNMF_EPI(EPI_MU)
+  PLNMF_EPI(EPI_OUT_GRAD)
 #undef PLNMF_EPI
-  if constexpr (epi_used<T, AT, BT>(EPI_RESID_SQ)) {
-    if (g.epi == EPI_RESID_SQ) {
-      double* red = (double*)gemm_lds;  // the operand tiles are no longer read
+  constexpr bool kSums = epi_used<T, AT, BT>(EPI_RESID_SQ) || epi_used<T, AT, BT>(EPI_OUT_GRAD);
+  constexpr bool kCols = epi_used<T, AT, BT>(EPI_GELU_GRAD) || epi_used<T, AT, BT>(EPI_OUT_GRAD);
+  double* red = (double*)gemm_lds;  // the operand tiles are no longer read
+  if constexpr (kSums) {
+    if (g.epi == EPI_RESID_SQ || g.epi == EPI_OUT_GRAD) {
       for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
       if (lane == 0) red[w] = ss;
       __syncthreads();
@@ -502,6 +516,23 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
         double t = 0.0;
         for (int i = 0; i < NTHR / 64; i++) t += red[i];
         g.red_out[(int64_t)ty * gridDim.x + tx] = t;
+      }
+    }
+  }
+  if constexpr (kCols) {
+    if (g.epi == EPI_GELU_GRAD || g.epi == EPI_OUT_GRAD) {
+      // the tile's column sums: a lane's rows, the other half's, then the wave rows
+      double* col = red + NTHR / 64;  // [wave row][BN]
+#pragma unroll
+      for (int j = 0; j < BJ; j++) {
+        const double t = cs[j] + __shfl_xor(cs[j], 32);
+        if (lane < 32) col[wm * BN + wn * 32 * BJ + 32 * j + lane] = t;
+      }
+      __syncthreads();
+      if (tid < BN && n0 + tid < N) {
+        double t = 0.0;
+        for (int i = 0; i < NTHR / 64 / NWN; i++) t += col[i * BN + tid];
+        g.col_part[(int64_t)tx * N + n0 + tid] = t;
       }
     }
   }
@@ -615,6 +646,7 @@ GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits) {
 }
 
 int gemm_tile_cols(int cfg) { return kCfg[cfg].BN; }
+int gemm_tile_rows(int cfg) { return kCfg[cfg].BM; }
 
 // The residual's partial sums: one per tile of the 128 x 128 form.
 int64_t gemm_resid_tiles(int64_t M, int64_t N) {
@@ -642,7 +674,7 @@ hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream
   const hipError_t e = t == Elem::F32 ? launch_elem<float>(a_trans, b_trans, g, far, g.cfg, s)
                                       : launch_elem<__bf16>(a_trans, b_trans, g, far, g.cfg, s);
   if (e != hipSuccess) return e;
-  if (g.splits > 1 && g.epi == EPI_STORE)
+  if (g.splits > 1 && g.epi == EPI_STORE && g.C)  // without C the caller sums the partials
     return splitk_reduce(g.partial, g.splits, g.M, g.N, g.C, g.ldc, g.bias, s);
   return hipSuccess;
 }

@@ -58,9 +58,11 @@ enum GemmEpi : int {
   EPI_RESID_SQ = 1,   // red_out[tile] = sum (D - acc)^2 over the tile (FP64)
   EPI_BIAS_GELU = 2,  // C = acc + bias (pre-activation, FP32; skipped if C is NULL); C2 (bf16) = GELU(C)
   EPI_BIAS_SOFTPLUS = 3, // C = acc + bias (FP32; skipped if NULL); C2 (float) = softplus(C)
-  EPI_GELU_GRAD = 4,  // C (FP32, if set) and C2 (bf16) = acc * GELU'(D), D = z1
+  EPI_GELU_GRAD = 4,  // C2 (bf16) = d = acc * GELU'(D), D = z1; col_part: sums of d
   EPI_MU = 5,         // C = D * X / (acc + mu_delta), X = (const float*)C2 (ld = ldc);
                       // C may be D (each element is read, then written, by one thread)
+  EPI_OUT_GRAD = 6,   // e = softplus(z) - D, z = acc + bias; C2 (bf16) = g = scale * e *
+                      // softplus'(z); red_out[tile] = sum e^2; col_part: sums of g
 };
 
 struct GemmArgs {
@@ -80,6 +82,8 @@ struct GemmArgs {
   int64_t k_per_split;
   float* partial;  // [splits][M][N]
   float mu_delta;  // EPI_MU: added to the denominator
+  float scale;     // EPI_OUT_GRAD
+  double* col_part;  // [M tiles][N] column sums over each tile's rows (FP64)
   int cfg;         // tile form (GemmPlan::cfg)
 };
 
@@ -99,6 +103,7 @@ hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream
 // splits * M * N floats when splits > 1).
 GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits = 256);
 int gemm_tile_cols(int cfg);  // columns of C that one workgroup computes
+int gemm_tile_rows(int cfg);
 int64_t gemm_resid_tiles(int64_t M, int64_t N);
 // C[M,N] (ldc) = sum_z partial[z] (+ bias[n])
 hipError_t splitk_reduce(const float* partial, int splits, int64_t M, int64_t N, float* C,
@@ -286,15 +291,28 @@ int hals_w_grid(int device_cus, int64_t rows, int K, int n_col);
 // ----------------------------------------------------------------- MLP ----
 hipError_t mlp_init_params(float* master, int64_t n, int K, int hidden, uint64_t seed,
                            hipStream_t s);
-hipError_t mlp_adam(float* master, float* m, float* v, const float* g, int64_t n, float lr,
-                    int64_t* step, hipStream_t s);
+// One Adam step, the BF16 copies of the two weight matrices written with it.
+hipError_t mlp_adam(float* master, float* m, float* v, const float* g, int K, int hidden, float lr,
+                    __bf16* w1b, __bf16* w2b, int64_t* step, hipStream_t s);
 hipError_t acc_scaled(double* acc, const double* v, double scale, hipStream_t s);
-hipError_t mlp_out_grad(const float* z2, const float* yhat, const float* y, int64_t n,
-                        float scale, __bf16* dz2_bf16, float* dz2_f32, double* loss_partial,
-                        int nblk, hipStream_t s);
-constexpr int kColSlices = 32;  // row slices of a column sum (part: kColSlices x cols doubles)
-hipError_t col_sum(const float* x, int64_t rows, int64_t cols, float* out, double* part,
-                   hipStream_t s);
+// What is left of one batch's gradients after the matrix products, in one launch:
+// the weight gradients' split sums, the bias gradients from the tiles' column sums
+// and the loss (each in a fixed order).
+struct MlpFinish {
+  const float* part2;   // [splits2][K H], or null: gW2 is complete
+  const float* part1;   // [splits1][H K]
+  int splits2, splits1;
+  int64_t n;            // K H
+  float *gW2, *gW1;
+  const double* col2;   // [tiles2][K]
+  const double* col1;   // [tiles1][H]
+  int tiles2, tiles1, K, H;
+  float *gb2, *gb1;
+  const double* red;    // [n_red] loss per tile
+  int n_red;
+  double* loss;
+};
+hipError_t mlp_finish(const MlpFinish& f, hipStream_t s);
 
 hipError_t gather_rows(const float* x, const int32_t* idx, int64_t n, int64_t cols, float* out,
                        hipStream_t s);

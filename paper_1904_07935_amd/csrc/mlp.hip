@@ -1,8 +1,14 @@
 // Kernels of the fold-in warm-start network around its matrix-core products
 // (the products themselves run through the shared GEMM with fused bias/GELU,
-// bias/softplus and GELU-gradient epilogues): seeded init, the output-layer
-// gradient of the mean-squared error, bias-gradient column sums, Adam, and the
-// row normalisation / rescaling that wraps the network in fold-in.
+// bias/softplus, output-gradient and GELU-gradient epilogues, which also leave the
+// loss and the bias gradients' column sums per tile): seeded init, the sums over
+// splits and tiles that finish a batch's gradients, Adam, and the row
+// normalisation / rescaling that wraps the network in fold-in.
+//
+// A training step is launch-bound (1,024 rows, K = 200, 512 hidden units: 19
+// launches of which none ran 15 us), so what follows a product lives in its
+// epilogue or shares one launch: 10 launches, from
+// 272 to 146 us with the GEMM tiles for small products (195 us with those alone).
 #include <algorithm>
 
 #include "internal.hpp"
@@ -30,13 +36,18 @@ __global__ void init_kernel(float* __restrict__ p, int64_t n, int K, int H, uint
 }
 
 // Adam with bias corrections for step t = *step + 1 (the count is bumped by a
-// separate one-thread launch afterwards)
-__global__ void adam_kernel(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, int64_t n, float lr,
-                            const int64_t* __restrict__ step) {
-  const double t = (double)(*step + 1);
-  const float b1t = (float)(1.0 - pow(0.9, t));
-  const float b2t = (float)(1.0 - pow(0.999, t));
+// separate one-thread launch afterwards); the updated weights also go to their
+// BF16 copies.  Masters: W1 [n1], b1 [H], W2 [n1], b2 [K].
+__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ p, float* __restrict__ m,
+                                                   float* __restrict__ v, const float* __restrict__ g,
+                                                   int64_t n, int64_t n1, int H, float lr,
+                                                   __bf16* __restrict__ w1b, __bf16* __restrict__ w2b,
+                                                   const int64_t* __restrict__ step) {
+  __shared__ float corr[2];
+  if (threadIdx.x < 2)
+    corr[threadIdx.x] = (float)(1.0 - pow(threadIdx.x ? 0.999 : 0.9, (double)(*step + 1)));
+  __syncthreads();
+  const float b1t = corr[0], b2t = corr[1];
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const float gi = g[i];
@@ -44,7 +55,10 @@ __global__ void adam_kernel(float* __restrict__ p, float* __restrict__ m, float*
     const float vi = 0.999f * v[i] + 0.001f * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / b1t) / (sqrtf(vi / b2t) + 1e-8f);
+    const float x = p[i] - lr * (mi / b1t) / (sqrtf(vi / b2t) + 1e-8f);
+    p[i] = x;
+    if (i < n1) w1b[i] = (__bf16)x;
+    else if (i >= n1 + H && i < 2 * n1 + H) w2b[i - n1 - H] = (__bf16)x;
   }
 }
 
@@ -52,51 +66,56 @@ __global__ void bump_kernel(int64_t* step) { *step += 1; }
 
 __global__ void acc_kernel(double* acc, const double* v, double scale) { acc[0] += v[0] * scale; }
 
-// d = yhat - y; loss partial sum d^2 (FP64); dz2 = scale * d * softplus'(z2)
-__global__ void out_grad_kernel(const float* __restrict__ z2, const float* __restrict__ yhat,
-                                const float* __restrict__ y, int64_t n, float scale,
-                                __bf16* __restrict__ dz2b, float* __restrict__ dz2f,
-                                double* __restrict__ part) {
-  __shared__ double sh[4];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float d = yhat[i] - y[i];
-    s += (double)d * (double)d;
-    const float z = z2[i];
-    const float sg = z > 20.0f ? 1.0f : 1.0f / (1.0f + expf(-z));
-    const float gz = scale * d * sg;
-    dz2b[i] = (__bf16)gz;
-    dz2f[i] = gz;
+// See MlpFinish.  Blocks: [0, nw) the weight gradients (2 n elements, in fours of
+// 256), then a wave per bias, then the loss.
+__global__ __launch_bounds__(256) void finish_grads_kernel(MlpFinish f, int nw, int nb) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int b = blockIdx.x;
+  if (b < nw) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int64_t i = (int64_t)b * 1024 + 256 * u + tid;
+      if (i >= 2 * f.n) break;
+      const bool two = i < f.n;
+      const int64_t e = two ? i : i - f.n;
+      const float* part = two ? f.part2 : f.part1;
+      if (!part) continue;
+      const int splits = two ? f.splits2 : f.splits1;
+      float t = 0.0f;
+      int z = 0;
+      for (; z + 3 < splits; z += 4) {  // four loads in flight, added in split order
+        const float a0 = part[z * f.n + e], a1 = part[(z + 1) * f.n + e];
+        const float a2 = part[(z + 2) * f.n + e], a3 = part[(z + 3) * f.n + e];
+        t += a0;
+        t += a1;
+        t += a2;
+        t += a3;
+      }
+      for (; z < splits; z++) t += part[z * f.n + e];
+      (two ? f.gW2 : f.gW1)[e] = t;
+    }
+    return;
   }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  b -= nw;
+  if (b < nb) {
+    const int c = 4 * b + w;  // bias index: b2, then b1
+    if (c >= f.K + f.H) return;
+    const bool two = c < f.K;
+    const double* col = two ? f.col2 + c : f.col1 + (c - f.K);
+    const int tiles = two ? f.tiles2 : f.tiles1, ld = two ? f.K : f.H;
+    double t = 0.0;
+    for (int i = lane; i < tiles; i += 64) t += col[(int64_t)i * ld];
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+    if (lane == 0) (two ? f.gb2[c] : f.gb1[c - f.K]) = (float)t;
+    return;
+  }
+  __shared__ double sh[4];
+  double t = 0.0;
+  for (int i = tid; i < f.n_red; i += 256) t += f.red[i];
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+  if (lane == 0) sh[w] = t;
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
-}
-
-// out[c] = sum_r x[r, c] in two fixed-order passes: slice s of the rows sums
-// its rows in order per column (FP64) into part[s][c], then the slices are
-// added in slice order.  Thread per column and workgroup per (column block,
-// row slice), so a batch of 1024 rows and 512 columns spreads over the chip.
-__global__ void colsum_part_kernel(const float* __restrict__ x, int64_t rows, int64_t cols,
-                                   int slices, double* __restrict__ part) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int sl = blockIdx.y;
-  if (c >= cols) return;
-  const int64_t r0 = rows * sl / slices, r1 = rows * (sl + 1) / slices;
-  double s = 0.0;
-  for (int64_t r = r0; r < r1; r++) s += x[r * cols + c];
-  part[(int64_t)sl * cols + c] = s;
-}
-
-__global__ void colsum_fin_kernel(const double* __restrict__ part, int64_t cols, int slices,
-                                  float* __restrict__ out) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  double s = 0.0;
-  for (int sl = 0; sl < slices; sl++) s += part[(int64_t)sl * cols + c];
-  out[c] = (float)s;
+  if (tid == 0) *f.loss = sh[0] + sh[1] + sh[2] + sh[3];
 }
 
 __global__ void gather_kernel(const float* __restrict__ x, const int32_t* __restrict__ idx,
@@ -347,9 +366,10 @@ hipError_t mlp_init_params(float* master, int64_t n, int K, int hidden, uint64_t
   return hipGetLastError();
 }
 
-hipError_t mlp_adam(float* master, float* m, float* v, const float* g, int64_t n, float lr,
-                    int64_t* step, hipStream_t s) {
-  adam_kernel<<<grid_for(n), 256, 0, s>>>(master, m, v, g, n, lr, step);
+hipError_t mlp_adam(float* master, float* m, float* v, const float* g, int K, int hidden, float lr,
+                    __bf16* w1b, __bf16* w2b, int64_t* step, hipStream_t s) {
+  const int64_t n1 = (int64_t)K * hidden, n = 2 * n1 + K + hidden;
+  adam_kernel<<<grid_for(n), 256, 0, s>>>(master, m, v, g, n, n1, hidden, lr, w1b, w2b, step);
   bump_kernel<<<1, 1, 0, s>>>(step);
   return hipGetLastError();
 }
@@ -359,20 +379,10 @@ hipError_t acc_scaled(double* acc, const double* v, double scale, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t mlp_out_grad(const float* z2, const float* yhat, const float* y, int64_t n,
-                        float scale, __bf16* dz2_bf16, float* dz2_f32, double* loss_partial,
-                        int nblk, hipStream_t s) {
-  out_grad_kernel<<<nblk, 256, 0, s>>>(z2, yhat, y, n, scale, dz2_bf16, dz2_f32, loss_partial);
-  return hipGetLastError();
-}
-
-hipError_t col_sum(const float* x, int64_t rows, int64_t cols, float* out, double* part,
-                   hipStream_t s) {
-  if (cols <= 0) return hipSuccess;
-  const int slices = (int)std::max<int64_t>(1, std::min<int64_t>(kColSlices, rows));
-  const unsigned cb = (unsigned)((cols + 255) / 256);
-  colsum_part_kernel<<<dim3(cb, (unsigned)slices), 256, 0, s>>>(x, rows, cols, slices, part);
-  colsum_fin_kernel<<<cb, 256, 0, s>>>(part, cols, slices, out);
+hipError_t mlp_finish(const MlpFinish& f, hipStream_t s) {
+  const int nw = f.part2 || f.part1 ? (int)((2 * f.n + 1023) / 1024) : 0;
+  const int nb = (f.K + f.H + 3) / 4;
+  finish_grads_kernel<<<(unsigned)(nw + nb + 1), 256, 0, s>>>(f, nw, nb);
   return hipGetLastError();
 }
 

@@ -62,17 +62,14 @@ struct Ws {
   __bf16* xb;
   float* z1;
   __bf16* gb;
-  float* z2;
-  float* yhat;
   __bf16* dz2b;
-  float* dz2f;
-  float* dz1f;
   __bf16* dz1b;
-  float* partial;
+  float* partial;   // split sums of gW2, then of gW1
   int max_splits;
-  double* red;
+  double* red;      // loss per tile
   double* scal;
-  double* csum;  // column-sum partials [kColSlices][max(K, H)]
+  double* col2;     // column sums per tile of rows
+  double* col1;
   float* grads;
   float* xbat;
   float* ybat;
@@ -84,23 +81,23 @@ struct Ws {
 // it never shrinks as the batch grows, which batch_of relies on
 int splits_for(int64_t B) { return (int)std::max<int64_t>(1, std::min<int64_t>(B / 64, 16)); }
 
+constexpr int64_t kTileRowsMin = 64;  // rows of the smallest GEMM tile
+
 Ws ws_layout(void* base, int K, int H, int64_t B) {
   Carver c(base);
   Ws w;
   w.xb = c.take<__bf16>((size_t)(B * K));
   w.z1 = c.take<float>((size_t)(B * H));
   w.gb = c.take<__bf16>((size_t)(B * H));
-  w.z2 = c.take<float>((size_t)(B * K));
-  w.yhat = c.take<float>((size_t)(B * K));
   w.dz2b = c.take<__bf16>((size_t)(B * K));
-  w.dz2f = c.take<float>((size_t)(B * K));
-  w.dz1f = c.take<float>((size_t)(B * H));
   w.dz1b = c.take<__bf16>((size_t)(B * H));
   w.max_splits = splits_for(B);
-  w.partial = c.take<float>((size_t)w.max_splits * K * H);
-  w.red = c.take<double>(1024);
+  w.partial = c.take<float>((size_t)2 * w.max_splits * K * H);
+  const int64_t mt = (B + kTileRowsMin - 1) / kTileRowsMin;
+  w.red = c.take<double>((size_t)(mt * ((K + 31) / 32)));
   w.scal = c.take<double>(8);
-  w.csum = c.take<double>((size_t)kColSlices * std::max(K, H));
+  w.col2 = c.take<double>((size_t)(mt * K));
+  w.col1 = c.take<double>((size_t)(mt * H));
   w.grads = c.take<float>((size_t)H * K + H + (size_t)K * H + K);
   w.xbat = c.take<float>((size_t)(B * K));
   w.ybat = c.take<float>((size_t)(B * K));
@@ -142,9 +139,9 @@ hipError_t refresh(const Params& p, int K, int H, hipStream_t s) {
   return cast_bf16(p.W2, p.W2b, (int64_t)K * H, s);
 }
 
-// forward of b rows of X (FP32) into yhat (FP32); leaves z1, gb, z2, xb in ws
-int forward_rows(const Params& p, int K, int H, const float* X, float* yhat, int64_t b,
-                 const Ws& w, hipStream_t s) {
+// loss (device scal[0], sum over b*K) and gradients of b rows into `grads`
+int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y, int64_t b,
+                   float* grads, const Ws& w, hipStream_t s) {
   MLPCHECK(cast_bf16(X, w.xb, b * K, s));
   GemmArgs g{};
   g.A = w.xb;
@@ -161,6 +158,7 @@ int forward_rows(const Params& p, int K, int H, const float* X, float* yhat, int
   g.C2 = w.gb;
   gemm_use(g, gemm_plan(Elem::BF16, g.M, g.N, g.Kd, 1));
   MLPCHECK(gemm(Elem::BF16, false, true, g, s));
+  // the output layer, its loss and dz2 = 2 / (b K) (yhat - y) softplus'(z2)
   GemmArgs g2{};
   g2.A = w.gb;
   g2.lda = H;
@@ -169,30 +167,22 @@ int forward_rows(const Params& p, int K, int H, const float* X, float* yhat, int
   g2.M = b;
   g2.N = K;
   g2.Kd = H;
-  g2.C = w.z2;
   g2.ldc = K;
-  g2.epi = EPI_BIAS_SOFTPLUS;
+  g2.epi = EPI_OUT_GRAD;
   g2.bias = p.b2;
-  g2.C2 = yhat;
+  g2.D = Y;
+  g2.ldd = K;
+  g2.C2 = w.dz2b;
+  g2.scale = (float)(2.0 / (double)(b * K));
+  g2.red_out = w.red;
+  g2.col_part = w.col2;
   gemm_use(g2, gemm_plan(Elem::BF16, g2.M, g2.N, g2.Kd, 1));
   MLPCHECK(gemm(Elem::BF16, false, true, g2, s));
-  return NMF_OK;
-}
-
-// loss (device scal[0], mean over b*K) and gradients into `grads`
-int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y, int64_t b,
-                   float* grads, const Ws& w, hipStream_t s) {
-  int rc = forward_rows(p, K, H, X, w.yhat, b, w, s);
-  if (rc) return rc;
-  const int64_t n = b * K;
-  const int nb = reduce_blocks(n);
-  MLPCHECK(mlp_out_grad(w.z2, w.yhat, Y, n, (float)(2.0 / (double)n), w.dz2b, w.dz2f, w.red, nb, s));
-  MLPCHECK(finish_f64(w.red, nb, w.scal, s));
   float* gW1 = grads;
   float* gb1 = gW1 + (size_t)H * K;
   float* gW2 = gb1 + H;
   float* gb2 = gW2 + (size_t)K * H;
-  // gW2 [K,H] = dz2^T g
+  // gW2 [K,H] = dz2^T g (split sums added by mlp_finish)
   GemmArgs a{};
   a.A = w.dz2b;  // A(k, r) = dz2[r*K + k]
   a.lda = K;
@@ -201,13 +191,12 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   a.M = K;
   a.N = H;
   a.Kd = b;
-  a.C = gW2;
   a.ldc = H;
   a.epi = EPI_STORE;
   gemm_use(a, gemm_plan(Elem::BF16, a.M, a.N, a.Kd, w.max_splits));
+  a.C = a.splits > 1 ? nullptr : gW2;
   a.partial = w.partial;
   MLPCHECK(gemm(Elem::BF16, true, false, a, s));
-  MLPCHECK(col_sum(w.dz2f, b, K, gb2, w.csum, s));
   // dz1 [b,H] = (dz2 W2) * GELU'(z1)
   GemmArgs d{};
   d.A = w.dz2b;
@@ -217,12 +206,12 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   d.M = b;
   d.N = H;
   d.Kd = K;
-  d.C = w.dz1f;
   d.ldc = H;
   d.epi = EPI_GELU_GRAD;
   d.D = w.z1;
   d.ldd = H;
   d.C2 = w.dz1b;
+  d.col_part = w.col1;
   gemm_use(d, gemm_plan(Elem::BF16, d.M, d.N, d.Kd, 1));
   MLPCHECK(gemm(Elem::BF16, false, false, d, s));
   // gW1 [H,K] = dz1^T x
@@ -234,13 +223,32 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   c.M = H;
   c.N = K;
   c.Kd = b;
-  c.C = gW1;
   c.ldc = K;
   c.epi = EPI_STORE;
   gemm_use(c, gemm_plan(Elem::BF16, c.M, c.N, c.Kd, w.max_splits));
-  c.partial = w.partial;
+  c.C = c.splits > 1 ? nullptr : gW1;
+  c.partial = w.partial + (size_t)w.max_splits * K * H;
   MLPCHECK(gemm(Elem::BF16, true, false, c, s));
-  MLPCHECK(col_sum(w.dz1f, b, H, gb1, w.csum, s));
+  MlpFinish f{};
+  f.part2 = a.splits > 1 ? a.partial : nullptr;
+  f.part1 = c.splits > 1 ? c.partial : nullptr;
+  f.splits2 = a.splits;
+  f.splits1 = c.splits;
+  f.n = (int64_t)K * H;
+  f.gW2 = gW2;
+  f.gW1 = gW1;
+  f.col2 = w.col2;
+  f.col1 = w.col1;
+  f.tiles2 = (int)((b + gemm_tile_rows(g2.cfg) - 1) / gemm_tile_rows(g2.cfg));
+  f.tiles1 = (int)((b + gemm_tile_rows(d.cfg) - 1) / gemm_tile_rows(d.cfg));
+  f.K = K;
+  f.H = H;
+  f.gb2 = gb2;
+  f.gb1 = gb1;
+  f.red = w.red;
+  f.n_red = f.tiles2 * ((K + gemm_tile_cols(g2.cfg) - 1) / gemm_tile_cols(g2.cfg));
+  f.loss = w.scal;
+  MLPCHECK(mlp_finish(f, s));
   return NMF_OK;
 }
 
@@ -419,8 +427,7 @@ int nmf_mlp_adam_step(void* params, int K, int hidden, const float* grads, float
   if (!params || !grads) return fail(NMF_E_ARG, "NULL argument");
   hipStream_t s = (hipStream_t)stream;
   const Params p = view(params, K, hidden);
-  MLPCHECK(mlp_adam(p.W1, p.m, p.v, grads, (int64_t)p.n, lr, p.step, s));
-  MLPCHECK(refresh(p, K, hidden, s));
+  MLPCHECK(mlp_adam(p.W1, p.m, p.v, grads, K, hidden, lr, p.W1b, p.W2b, p.step, s));
   return NMF_OK;
 }
 
@@ -456,8 +463,7 @@ int nmf_mlp_train(void* params, int K, int hidden, const float* X, const float* 
       rc = loss_grad_rows(p, K, hidden, w.xbat, w.ybat, b, w.grads, w, s);
       if (rc) return rc;
       MLPCHECK(acc_scaled(w.scal + 1, w.scal, 1.0 / (double)(b * K), s));
-      MLPCHECK(mlp_adam(p.W1, p.m, p.v, w.grads, (int64_t)p.n, lr, p.step, s));
-      MLPCHECK(refresh(p, K, hidden, s));
+      MLPCHECK(mlp_adam(p.W1, p.m, p.v, w.grads, K, hidden, lr, p.W1b, p.W2b, p.step, s));
       nbatches++;
     }
     // the index uploads read `perm`, which the next epoch reshuffles
