@@ -87,8 +87,8 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
 }
 
 hipError_t gram_with(const float* X, int64_t rows, int K, float* out, float* gpart, int cus,
-                     hipStream_t s, float* panel = nullptr, int tile = 32, bool rows_layout = false) {
-  return gram_xtx(X, rows, K, out, K, gpart, cus, s, panel, 1, tile, rows_layout);
+                     hipStream_t s, float* panel = nullptr, int tile = 32, int order = kPanelPlain) {
+  return gram_xtx(X, rows, K, out, K, gpart, cus, s, panel, 1, tile, order);
 }
 
 #define FCHECK(expr)                                                                      \
@@ -220,8 +220,8 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
   FCHECK(hipMemsetAsync(f.panel, 0,
                         std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),
                                  hals_panel_floats(K, 64)) * sizeof(float), s));
-  const bool rl = hals_h_rows_layout(Dn, K, p->cus, p->h_tile);
-  FCHECK(gram_with(p->W, p->V, K, f.S, f.gpart, p->cus, s, f.panel, p->h_tile, rl));
+  const int order = hals_h_order(Dn, K, p->cus, p->h_tile);
+  FCHECK(gram_with(p->W, p->V, K, f.S, f.gpart, p->cus, s, f.panel, p->h_tile, order));
 
   // initialisation of H for the new documents
   if (init_mode == NMF_FOLDIN_WTA) {
@@ -242,7 +242,7 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
   a.diag_one = 1;
   a.panel = f.panel;
   a.tile = p->h_tile;
-  a.rows_layout = rl;
+  a.order = order;
   int filled = 0;  // trace entries waiting in f.trace
   int written = 0; // trace entries copied to the host
   auto flush = [&]() -> int {

@@ -422,6 +422,27 @@ __device__ __forceinline__ void put_panel_rows(float* panel, int K, int diag_one
     pt[(int64_t)nb * nt * 1024 + (c & 1) * (tile * tile / 2) + t * (tile / 2) + (c >> 1)] = v;
 }
 
+// The same entries in the H split kernel's order (tiles of 32): per tile the three
+// BF16 parts of the panel, [part][l / 8][column][l % 8] with l < 32 NT, then
+// G[t][c] for c > t (zero elsewhere).
+__device__ __forceinline__ void put_panel_split(float* panel, int K, int diag_one, int l, int col, float v) {
+  const int nt = (K + 31) / 32, j = col / 32, c = col % 32, a0 = 32 * j;
+  float pv;
+  if (l == col) pv = diag_one ? 1.0f - v : 0.0f;
+  else if (l >= a0 && l < col) pv = 0.0f;
+  else pv = -v;
+  unsigned char* tile = (unsigned char*)panel + (size_t)j * (3 * 32 * nt * 32 * 2 + 32 * 32 * 4);
+  unsigned short* parts = (unsigned short*)tile;
+  const unsigned x[8] = {__float_as_uint(pv), 0, 0, 0, 0, 0, 0, 0};
+  uintx4 p[3];
+  split8(x, p[0], p[1], p[2]);
+#pragma unroll
+  for (int q = 0; q < 3; q++)
+    parts[((q * 4 * nt + l / 8) * 32 + c) * 8 + l % 8] = (unsigned short)(p[q][0] & 0xffffu);
+  const int t = l - a0;
+  if (l / 32 == j && c > t) ((float*)(tile + (size_t)3 * 32 * nt * 32 * 2))[t * 32 + c] = v;
+}
+
 __device__ __forceinline__ void put_panel(float* panel, int K, int diag_one, int tile, int l, int col,
                                           float v) {
   const int kp = (K + 7) / 8 * 8, ntiles = (K + tile - 1) / tile;
@@ -438,7 +459,7 @@ __device__ __forceinline__ void put_panel(float* panel, int K, int diag_one, int
 __global__ __launch_bounds__(kRedThreads) void gram_reduce(const float* __restrict__ partial, int nchunks,
                                                     int K, float* __restrict__ C, int64_t ldc,
                                                     float* __restrict__ panel, int diag_one, int tile,
-                                                    int rows_layout) {
+                                                    int order) {
   __shared__ floatx4 part[kRedThreads];
   const int nb = nblk(K), nu = upper_blocks(K);
   const int u = blockIdx.x / 8, piece = blockIdx.x % 8;
@@ -482,7 +503,10 @@ __global__ __launch_bounds__(kRedThreads) void gram_reduce(const float* __restri
       if (gi <= gj && gj < K) {
         C[(int64_t)gi * ldc + gj] = tot[e];
         if (gi != gj) C[(int64_t)gj * ldc + gi] = tot[e];
-        if (panel && rows_layout) {
+        if (panel && order == kPanelSplit) {
+          put_panel_split(panel, K, diag_one, gi, gj, tot[e]);
+          if (gi != gj) put_panel_split(panel, K, diag_one, gj, gi, tot[e]);
+        } else if (panel && order == kPanelRows) {
           put_panel_rows(panel, K, diag_one, tile, gi, gj, tot[e]);
           if (gi != gj) put_panel_rows(panel, K, diag_one, tile, gj, gi, tot[e]);
         } else if (panel) {
@@ -577,7 +601,7 @@ hipError_t launch_fp32_width(const float* X, int64_t rows, int K, int cus, float
 }  // namespace
 
 hipError_t gram_xtx(const float* X, int64_t rows, int K, float* C, int64_t ldc, float* partial,
-                    int cus, hipStream_t s, float* panel, int diag_one, int tile, bool rows_layout) {
+                    int cus, hipStream_t s, float* panel, int diag_one, int tile, int order) {
   if (K <= 0) return hipSuccess;
   if (K > kMaxK || rows < 1) return hipErrorInvalidValue;
   int chunks = 1;
@@ -593,7 +617,7 @@ hipError_t gram_xtx(const float* X, int64_t rows, int K, float* C, int64_t ldc, 
   }
   if (e != hipSuccess) return e;
   gram_reduce<<<(unsigned)(upper_blocks(K) * 8), kRedThreads, 0, s>>>(partial, chunks, K, C, ldc, panel,
-                                                                diag_one, tile, rows_layout ? 1 : 0);
+                                                                diag_one, tile, order);
   return hipGetLastError();
 }
 

@@ -47,8 +47,10 @@
 // tagged flags over device-scope (XCD-coherent) loads and stores.  All waits are
 // bounded: on a timeout a status bit is set, every group stops waiting, and
 // the kernel still runs to completion.
+#include <algorithm>
 #include <cstdlib>
 
+#include "bf16x3.hpp"
 #include "internal.hpp"
 
 namespace plnmf {
@@ -143,8 +145,6 @@ __device__ void wait_flags(const unsigned* flags, int n, int stride, unsigned ta
 // L2 write-back or invalidation is needed.  The producer waits until its
 // stores are complete before it raises the flag.
 constexpr int kThrough = 16;  // buffer cache-policy bit sc1 (device scope)
-
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t store_view(void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
@@ -856,6 +856,294 @@ hipError_t h_rows_dispatch(const HalsArgs& b, bool vec, hipStream_t s) {
   return h_rows_tt<32>(b, vec, s);
 }
 
+// Split variant for very many rows.  The tile products run on the BF16 matrix
+// cores with every FP32 value of X and of the panel split into three BF16 parts
+// (bf16x3.hpp), six part products instead of one FP32 product at 16 times its
+// rate.  A workgroup is eight waves of 16 rows.  A wave keeps its rows' parts in
+// VGPRs for the whole sweep as A operands of v_mfma_f32_16x16x32_bf16: lane (m, g),
+// m = lane % 16, g = lane / 16, holds columns 32 t + 8 g .. + 7 of row m in xa[t].
+// The Gram writes the panels already split, in the order the lanes read them
+// ([part][l / 8][column][l % 8]); a tile's panel is copied into the LDS by
+// direct global-to-LDS loads while the tile before it is in phase 2.
+//
+// Phase 2 runs on the product's own output layout: lane (n, g) holds columns n
+// and 16 + n of rows 4 g .. 4 g + 3.  Column t's four values per lane row reach
+// the row's 16 lanes by a DPP row broadcast in the clip; G rows are zero up to
+// the diagonal, so a finished column keeps its unclipped value and is clipped
+// once more when it is written.  The finished tile goes through a few LDS rows
+// into operand order, is split there, and is stored to X.
+//
+// Why 16 rows per wave: two waves per SIMD fit (12 registers per 32 columns and
+// row), and one wave's phase 2 fills the other's matrix-core time.  Bounds: the
+// LDS reads of the panel (every wave reads all of it: 3 KB per 96 matrix-core
+// cycles) and the matrix cores are about equal, then phase 2.  Measured on
+// 300,000 x 400: 1,410 -> 960 us (FP32 rows kernel before); 100,000 x 200: 222 ->
+// 140 us.  Per tile at K = 400, cycles of both waves of a SIMD: product 9,300 (7,900
+// with the panel reads left out), phase 2 5,000, the rest 1,500.
+constexpr int kRowsSP = 16, kWavesSP = 8;
+constexpr int kTrP = 36;  // pitch of the transpose rows
+__host__ __device__ constexpr size_t sp_panel_bytes(int NT) { return (size_t)3 * 32 * NT * 32 * 2; }
+__host__ __device__ constexpr size_t sp_tile_bytes(int NT) { return sp_panel_bytes(NT) + T * T * 4; }
+__host__ __device__ constexpr size_t sp_smem_bytes(int NT) {
+  return sp_panel_bytes(NT) + 2 * T * T * 4 + (size_t)kWavesSP * kRowsSP * kTrP * 4;
+}
+
+// x[i] = max(eps, lane N of each row of 16 of y[i]), in all 16 lanes: one
+// instruction each, which the compiler does not form (it puts a move and a
+// quieting max before the max).  A DPP operand must have been written two wait
+// states before: one s_nop for the four.
+template <int N>
+__device__ __forceinline__ void clip_bcast(float (&x)[4], const float (&y)[4], float eps) {
+  asm("s_nop 1\n\t"
+      "v_max_f32_dpp %0, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %2, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %3, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+      : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3])
+      : "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]), "v"(eps), "n"(N));
+}
+
+// Steps 8 G .. 8 G + 7 of phase 2: y[b][i] is row 4 g + i, column 16 b + n; gr: the
+// steps' G rows at those columns.
+template <int G, int S = 0>
+__device__ __forceinline__ void sp_steps(float (&y)[2][4], const float (&gr)[8][2], float eps) {
+  if constexpr (S < 8) {
+    constexpr int B = G / 2;
+    float x[4];
+    clip_bcast<(8 * G + S) % 16>(x, y[B], eps);
+#pragma unroll
+    for (int b = B; b < 2; b++)
+#pragma unroll
+      for (int i = 0; i < 4; i++) y[b][i] -= x[i] * gr[S][b];
+    sp_steps<G, S + 1>(y, gr, eps);
+  }
+}
+template <int G>
+__device__ __forceinline__ void sp_rows(float (&gr)[8][2], const float* gl) {
+#pragma unroll
+  for (int s = 0; s < 8; s++)
+#pragma unroll
+    for (int b = G / 2; b < 2; b++) gr[s][b] = gl[(8 * G + s) * T + 16 * b];
+}
+// groups of 8 steps up to the tile's width, each group's G rows read during the
+// one before
+template <int G>
+__device__ __forceinline__ void sp_phase2(float (&y)[2][4], float (&gr)[8][2], const float* gl, float eps, int tw) {
+  if constexpr (G < T / 8) {
+    if (8 * G >= tw) return;
+    float gn[8][2];
+    if constexpr (G + 1 < T / 8) sp_rows<G + 1>(gn, gl);
+    asm volatile("" ::: "memory");
+    sp_steps<G>(y, gr, eps);
+    sp_phase2<G + 1>(y, gn, gl, eps, tw);
+  }
+}
+
+template <int NT, bool VEC>
+__global__ __launch_bounds__(64 * kWavesSP, 2) void hals_h_split_kernel(HalsArgs a) {
+  extern __shared__ __align__(16) unsigned char sp_lds[];
+  constexpr int K8 = 4 * NT;
+  uintx4* panel = (uintx4*)sp_lds;                              // [3][K8][32]
+  float* gbuf = (float*)(sp_lds + sp_panel_bytes(NT));          // [2][T][T]
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* tr = gbuf + 2 * T * T + w * kRowsSP * kTrP;            // this wave's [16][kTrP]
+  const int K = a.K, ntiles = (K + T - 1) / T;
+  const int64_t row0 = ((int64_t)blockIdx.x * kWavesSP + w) * kRowsSP;
+  const int nr = a.rows - row0 < kRowsSP ? (int)(a.rows - row0) : kRowsSP;  // may be <= 0
+  const float eps = a.eps;
+
+  // Tile j's panel and G block into the LDS, 1 KB per wave and instruction
+  // (wave-uniform LDS address, 16 bytes per lane)
+  auto stage = [&](int j) {
+    const char* src = (const char*)a.panel + (size_t)j * sp_tile_bytes(NT);
+#pragma unroll
+    for (int c = 0; c < (int)((sp_tile_bytes(NT) / 1024 + kWavesSP - 1) / kWavesSP); c++) {
+      const int piece = c * kWavesSP + w;
+      if (piece < (int)(sp_panel_bytes(NT) / 1024)) {
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(src + piece * 1024 + lane * 16),
+            (__attribute__((address_space(3))) void*)(sp_lds + piece * 1024), 16, 0, 0);
+      } else if (piece < (int)(sp_tile_bytes(NT) / 1024)) {
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(src + piece * 1024 + lane * 16),
+            (__attribute__((address_space(3))) void*)(sp_lds + piece * 1024 + (j & 1) * T * T * 4), 16, 0, 0);
+      }
+    }
+  };
+  stage(0);
+
+  // buffer views of the wave's rows of X and of Bterm: rows past the matrix read
+  // as zeros; columns past K (the last 32 only) hold the next row's values and
+  // are cleared in X, harmless in Bterm (their results are not used)
+  const int64_t wave_bytes = nr > 0 ? (int64_t)nr * K * 4 : 0;
+  const int64_t base = nr > 0 ? row0 * K : 0;
+  const __amdgpu_buffer_rsrc_t xv = tile_view(a.X + base, wave_bytes);
+  const __amdgpu_buffer_rsrc_t bv = tile_view(a.Bterm + base, wave_bytes);
+  uintx4 xa[NT][3];
+#pragma unroll
+  for (int t = 0; t < NT; t++) {
+    unsigned x[8];
+    const int c = 32 * t + 8 * g;
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const uintx4 v = ld16(xv, (uint32_t)(m * K + c + 4 * q) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[4 * q + e] = t < NT - 1 || c + 4 * q + e < K ? v[e] : 0u;
+    }
+    split8(x, xa[t][0], xa[t][1], xa[t][2]);
+  }
+  float bt[2][4];
+  auto load_bt = [&](int a0) {
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        bt[b][i] = __uint_as_float(ld4(bv, (uint32_t)((4 * g + i) * K + a0 + 16 * b + m) * 4));
+  };
+  load_bt(0);
+  float xs[8];  // the finished tile's columns 8 g .. 8 g + 7 of row m, stored a tile late
+  auto store_tile = [&](int j) {
+    const int a0 = j * T, c = a0 + 8 * g;
+    if (m >= nr) return;
+    float* dst = a.X + (row0 + m) * K + c;
+    if (VEC && a0 + T <= K) {
+      *(floatx4*)dst = floatx4{xs[0], xs[1], xs[2], xs[3]};
+      *(floatx4*)(dst + 4) = floatx4{xs[4], xs[5], xs[6], xs[7]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; e++)
+        if (c + e < K) dst[e] = xs[e];
+    }
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the staged panel is in the LDS
+  __syncthreads();
+
+#pragma unroll 1
+  for (int j = 0; j < ntiles; j++) {
+    const int a0 = j * T, tw = a0 + T < K ? T : K - a0;
+    if (j > 0) store_tile(j - 1);
+    floatx4 acc[2];
+    acc[0] = acc[1] = floatx4{0, 0, 0, 0};
+    const uintx4* pl = panel + g * 32 + m;
+    // step t's panel parts are read during step t - 1 where the registers allow
+    constexpr bool AHEAD = NT <= 13;
+    bf16x8 p[AHEAD ? 2 : 1][3][2];
+    auto read = [&](int t, bf16x8 (&d)[3][2]) {
+#pragma unroll
+      for (int q = 2; q >= 0; q--)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+          d[q][b] = __builtin_bit_cast(bf16x8, pl[(q * K8 + 4 * t) * 32 + 16 * b]);
+    };
+    if constexpr (AHEAD) read(0, p[0]);
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      if constexpr (AHEAD) {
+        if (t + 1 < NT) read(t + 1, p[(t + 1) & 1]);
+        asm volatile("" ::: "memory");
+      } else {
+        read(t, p[0]);
+      }
+      const bf16x8(&c)[3][2] = p[AHEAD ? t & 1 : 0];
+      auto mul = [&](int u, int q) {
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[t][u]), c[q][b], acc[b],
+                                                           0, 0, 0);
+      };
+      mul(2, 0);  // the small parts first
+      mul(0, 2);
+      mul(1, 1);
+      mul(1, 0);
+      mul(0, 1);
+      mul(0, 0);
+    }
+    __syncthreads();  // every wave is done with the panel
+    float y[2][4];
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int i = 0; i < 4; i++) y[b][i] = acc[b][i] + bt[b][i];
+    if (j + 1 < ntiles) {
+      stage(j + 1);
+      load_bt(a0 + T);
+    }
+    {
+      const float* gl = gbuf + (j & 1) * T * T + m;
+      float gr[8][2];
+      sp_rows<0>(gr, gl);
+      sp_phase2<0>(y, gr, gl, eps, tw);
+    }
+    // into operand order: row m, columns 8 g .. 8 g + 7
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        tr[(4 * g + i) * kTrP + 16 * b + m] = 16 * b + m < tw ? fmaxf(eps, y[b][i]) : 0.0f;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    unsigned x[8];
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const floatx4 v = *(const floatx4*)(tr + m * kTrP + 8 * g + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        xs[4 * q + e] = v[e];
+        x[4 * q + e] = __float_as_uint(v[e]);
+      }
+    }
+    uintx4 ph, pm, plo;
+    split8(x, ph, pm, plo);
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+      if (t == j) {  // uniform
+        xa[t][0] = ph;
+        xa[t][1] = pm;
+        xa[t][2] = plo;
+      }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next panel is in the LDS
+    __syncthreads();
+  }
+  store_tile(ntiles - 1);
+}
+
+template <int NT>
+hipError_t launch_h_split(const HalsArgs& b, bool vec, hipStream_t s) {
+  const unsigned grid = (unsigned)((b.rows + kWavesSP * kRowsSP - 1) / (kWavesSP * kRowsSP));
+  constexpr size_t bytes = sp_smem_bytes(NT);
+  static_assert(bytes <= kRrLdsMax && sp_tile_bytes(NT) % 1024 == 0, "staging");
+  const void* fn = vec ? (const void*)hals_h_split_kernel<NT, true> : (const void*)hals_h_split_kernel<NT, false>;
+  hipError_t e = allow_smem(fn, bytes);
+  if (e != hipSuccess) return e;
+  if (vec) hals_h_split_kernel<NT, true><<<grid, 64 * kWavesSP, bytes, s>>>(b);
+  else hals_h_split_kernel<NT, false><<<grid, 64 * kWavesSP, bytes, s>>>(b);
+  return hipGetLastError();
+}
+
+hipError_t h_split_dispatch(const HalsArgs& b, bool vec, hipStream_t s) {
+  switch ((b.K + 31) / 32) {
+    case 1: return launch_h_split<1>(b, vec, s);
+    case 2: return launch_h_split<2>(b, vec, s);
+    case 3: return launch_h_split<3>(b, vec, s);
+    case 4: return launch_h_split<4>(b, vec, s);
+    case 5: return launch_h_split<5>(b, vec, s);
+    case 6: return launch_h_split<6>(b, vec, s);
+    case 7: return launch_h_split<7>(b, vec, s);
+    case 8: return launch_h_split<8>(b, vec, s);
+    case 9: return launch_h_split<9>(b, vec, s);
+    case 10: return launch_h_split<10>(b, vec, s);
+    case 11: return launch_h_split<11>(b, vec, s);
+    case 12: return launch_h_split<12>(b, vec, s);
+    case 13: return launch_h_split<13>(b, vec, s);
+    case 14: return launch_h_split<14>(b, vec, s);
+    case 15: return launch_h_split<15>(b, vec, s);
+    case 16: return launch_h_split<16>(b, vec, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // ---------------------------------------------------------------- W half ----
 
 constexpr int kWThreads = 512;
@@ -1437,16 +1725,22 @@ static bool h_rows_kernel_for(int64_t rows, int K, int cus) {
 }
 
 size_t hals_panel_floats(int K, int tile) {
-  // the larger of the two orders: [tile][row][column] + the G blocks, or the
-  // rows kernel's staging blocks (rows padded to 32 NT)
+  // the largest of the orders: [tile][row][column] + the G blocks, or the rows
+  // kernels' staging blocks (rows padded to 32 NT)
   const int ntiles = (K + tile - 1) / tile;
   const size_t plain = (size_t)ntiles * kpad(K) * tile + (size_t)ntiles * tile * tile;
   const size_t rows = (size_t)ntiles * rr_stage_floats((K + 31) / 32, tile);
-  return plain > rows ? plain : rows;
+  const size_t split = tile == T ? (size_t)ntiles * sp_tile_bytes((K + 31) / 32) / 4 : 0;
+  return std::max(std::max(plain, rows), split);
 }
 
-bool hals_h_rows_layout(int64_t rows, int K, int cus, int tile) {
-  return (tile != 0 && tile != T) || h_rows_kernel_for(rows, K, cus);
+// From 65,536 rows on the split kernel.  Below, the FP32 kernels: their sums keep
+// the trajectory of a small sparse corpus, whose weak components amplify the last
+// bit of H some tenfold per half, and a sweep of one spends little time here.
+int hals_h_order(int64_t rows, int K, int cus, int tile) {
+  const bool forced = getenv("NMF_H_KERNEL") != nullptr;
+  if ((tile == 0 || tile == T) && rows >= 65536 && !forced) return kPanelSplit;
+  return (tile != 0 && tile != T) || h_rows_kernel_for(rows, K, cus) ? kPanelRows : kPanelPlain;
 }
 
 bool hals_tile_supported(int K, int tile) {
@@ -1468,7 +1762,8 @@ hipError_t hals_update(const HalsArgs& a, hipStream_t s) {
   const bool vec = (a.K % 4 == 0) && (((uintptr_t)a.X & 15) == 0);
   if (tile != T && !vec) return hipErrorInvalidValue;
   // widths other than 32: the rows-in-registers kernel only
-  if (a.rows_layout) return h_rows_dispatch(b, vec, s);
+  if (a.order == kPanelSplit) return tile == T ? h_split_dispatch(b, vec, s) : hipErrorInvalidValue;
+  if (a.order == kPanelRows) return h_rows_dispatch(b, vec, s);
   if (tile != T) return hipErrorInvalidValue;  // other widths: the rows kernel only
   const size_t bytes = h_smem_floats(a.K) * 4;
   const void* fn = vec ? (const void*)hals_h_kernel<true> : (const void*)hals_h_kernel<false>;

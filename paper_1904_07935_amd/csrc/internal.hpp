@@ -120,11 +120,15 @@ size_t gram_partial_floats(int K);  // scratch for any number of rows
 // With `panel` set, also writes the tile panels of the column updates derived
 // from C (hals_panel_floats(K) floats; entries that never depend on C -- rows
 // >= K, and outside the last tile -- must have been zeroed once), in the
-// [tile][row][column] order with the tiles' G blocks after them, or with
-// `rows_layout` in the H rows kernel's staging order (hals_h_rows_layout).
+// order of the H kernel that reads them.
+enum PanelOrder : int {
+  kPanelPlain = 0,  // [tile][row][column] with the tiles' G blocks after them
+  kPanelRows = 1,   // the H rows kernel's staging order
+  kPanelSplit = 2,  // the H split kernel's: three BF16 parts, then the G block, per tile
+};
 hipError_t gram_xtx(const float* X, int64_t rows, int K, float* C, int64_t ldc, float* partial,
                     int cus, hipStream_t s, float* panel = nullptr, int diag_one = 0,
-                    int tile = 32, bool rows_layout = false);
+                    int tile = 32, int order = kPanelPlain);
 
 // ------------------------------------------------------------------ SpMM ----
 // out[r, 0:K] = sum_j val[j] X[col[j], 0:K] over the rows of a CSR matrix.
@@ -240,15 +244,15 @@ struct HalsArgs {
   const float* panel;    // tile panels of G (gram_xtx with panel output, diag_one and tile as here)
   const float* gblk;     // set by hals_update
   int tile;              // tile width: 32 (0 = 32), 16 or 64 (see hals_tile_supported)
-  int rows_layout;       // panel written in the rows kernel's order: that kernel runs
+  int order;             // PanelOrder of the panel
 };
 // Row-independent update (no normalisation): the H half and fold-in.
 hipError_t hals_update(const HalsArgs& a, hipStream_t s);
 size_t hals_panel_floats(int K, int tile = 32);
-// Whether the H update of `rows` rows takes the rows-in-registers kernel (so
-// its Gram writes the panel in that kernel's staging order): decided once by
-// the caller, passed to gram_xtx and to hals_update (HalsArgs::rows_layout).
-bool hals_h_rows_layout(int64_t rows, int K, int cus, int tile);
+// The order of the panel that the H update of `rows` rows reads (and so which
+// kernel it takes): decided once by the caller, passed to gram_xtx and to
+// hals_update (HalsArgs::order).
+int hals_h_order(int64_t rows, int K, int cus, int tile);
 // Tile widths of the H update: 32 always; 16 and 64 when K % 4 == 0 and the
 // rows-in-registers kernel's double-buffered panel fits the LDS.
 bool hals_tile_supported(int K, int tile);

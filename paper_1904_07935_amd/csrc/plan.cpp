@@ -250,12 +250,12 @@ int plnmf::device_check(int* dev, int* cus) {
 
 // ------------------------------------------------------- step launchers ----
 hipError_t plnmf::gram(nmf_plan_s* p, const float* X, int64_t rows, float* out, int panel_diag,
-                       bool rows_layout) {
+                       int order) {
   // panel_diag 1: the H update's panels (its own buffer and tile width, in
   // the order of the kernel that will read them); 0: the W update's (32 wide)
   float* panel = panel_diag == 1 ? p->panel_h : panel_diag == 0 ? p->panel : nullptr;
   return gram_xtx(X, rows, p->K, out, p->K, p->gram_part, p->cus, p->stream,
-                  panel, panel_diag, panel_diag == 1 ? p->h_tile : kTile, panel_diag == 1 && rows_layout);
+                  panel, panel_diag, panel_diag == 1 ? p->h_tile : kTile, panel_diag == 1 ? order : (int)kPanelPlain);
 }
 
 namespace {
@@ -427,14 +427,14 @@ void prof_clear(nmf_plan_s* p) {
 }
 
 int half_h(nmf_plan_s* p) {
-  const bool rl = hals_h_rows_layout(p->D, p->K, p->cus, p->h_tile);
-  if (p->h_panel_order >= 0 && p->h_panel_order != (rl ? 1 : 0)) {
+  const int order = hals_h_order(p->D, p->K, p->cus, p->h_tile);
+  if (p->h_panel_order >= 0 && p->h_panel_order != order) {
     // the kernel choice changed (NMF_H_KERNEL): the other order's entries go
     const hipError_t e = hipMemsetAsync(p->panel_h, 0, p->panel_h_floats * sizeof(float), p->stream);
     if (e != hipSuccess) return fail(NMF_E_HIP, "hipMemsetAsync: %s", hipGetErrorString(e));
   }
-  p->h_panel_order = rl ? 1 : 0;
-  TIMED(p, NMF_STEP_GRAM_S, gram(p, p->W, p->V, p->S, 1, rl));  // + the H update's panels
+  p->h_panel_order = order;
+  TIMED(p, NMF_STEP_GRAM_S, gram(p, p->W, p->V, p->S, 1, order));  // + the H update's panels
   TIMED(p, NMF_STEP_PRODUCT_R, product_R(p));
   HalsArgs a{};
   a.X = p->Ht;
@@ -446,7 +446,7 @@ int half_h(nmf_plan_s* p) {
   a.diag_one = 1;
   a.panel = p->panel_h;
   a.tile = p->h_tile;
-  a.rows_layout = rl;
+  a.order = order;
   TIMED(p, NMF_STEP_UPDATE_H, hals_update(a, p->stream));
   p->pq_valid = false;
   return NMF_OK;

@@ -6,10 +6,10 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import rel_fro
+from tests.gpu_util import bf16_round, rel_fro
 from oracle import mlp as omlp
 from paper_1904_07935_amd.api import Mlp
-from test_gpu_foldin_mlp import _bf16_params, _net, _np, bf16_round
+from tests.test_gpu_foldin_mlp import _bf16_params, _net, _np
 
 pytestmark = pytest.mark.gpu
 
