@@ -60,6 +60,25 @@ __device__ __forceinline__ float ld_val(const void* p, int64_t j) {
   return (float)((const T*)p)[j];
 }
 
+// 16 bytes at any float's address
+typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// VEC: FP32 rows of any rank from 4 on are read and written 16 bytes at a time,
+// which needs 4-byte alignment only.  At a rank not divisible by 4 the last
+// lane takes columns K-4..K-1 and repeats sums of its neighbour's: the same
+// loads in the same order, so both write the same bits.  On 6,037 x 2,741
+// with 165,000 nonzeros at K = 77 (both products): 65 us with scalar loads, 43 so.
+// BF16: K % 4 == 0 and 8-byte alignment.
+__device__ __forceinline__ void st_x4(float* row, int c, int K, bool vec, floatx4 v) {
+  if (vec) {
+    if (c < K) *(any4*)(row + min(c, K - 4)) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (c + e < K) row[c + e] = v[e];
+  }
+}
+
 // Load 4 consecutive elements of a factor row (columns c..c+3) as floats.
 template <typename TX, bool VEC>
 __device__ __forceinline__ floatx4 ld_x4(const TX* row, int c, int K) {
@@ -67,7 +86,7 @@ __device__ __forceinline__ floatx4 ld_x4(const TX* row, int c, int K) {
   if constexpr (VEC) {
     if (c < K) {
       if constexpr (sizeof(TX) == 4) {
-        r = *(const floatx4*)(row + c);
+        r = *(const any4*)(row + min(c, K - 4));
       } else {
         bf16x4 b = *(const bf16x4*)(row + c);
         r = floatx4{(float)b[0], (float)b[1], (float)b[2], (float)b[3]};
@@ -131,44 +150,60 @@ __device__ __forceinline__ void wave_items(const SpmmKArgs& a, F work) {
   }
 }
 
+// The item's nonzeros row by row, NPAR side by side.  Few items are in flight on
+// small inputs, so a row's chain of loads sets the time: eight gathers a step,
+// the indices of the next step (of the next row, at a row's end) read one step
+// ahead, and the last step of a row filled up with zeros (0 * 0 added leaves a
+// sum as it is) instead of taken one nonzero at a time.  On 6,037 x
+// 2,741 with 165,000 nonzeros at K = 77 (both products), with the items of half the
+// size that spmm_build makes there: 43 -> 22 us.
 template <int VPL, int LPN, typename TV, typename TX, bool VEC>
 __device__ __forceinline__ void items_wave(const SpmmKArgs& a, const int4 item, const int slot) {
   constexpr int NPAR = 64 / LPN;  // nonzeros processed side by side per wave
-  constexpr int UNR = 4;
+  constexpr int UNR = VPL == 1 && LPN >= 16 ? 8 : 4;
   const int lane = threadIdx.x & 63;
   const int grp = lane / LPN, q = lane % LPN;
   const int K = a.K;
   const TX* X = (const TX*)a.X;
+  int32_t cc[UNR];
+  float vv[UNR];
+  auto fetch = [&](int64_t j, int64_t end) {
+#pragma unroll
+    for (int u = 0; u < UNR; u++) {
+      const bool in = j + u * NPAR < end;
+      cc[u] = in ? a.col[j + u * NPAR] : -1;
+      vv[u] = in ? ld_val<TV>(a.val, j + u * NPAR) : 0.0f;
+    }
+  };
+  int64_t rs = item.z, re = min(a.rowptr[item.x + 1], item.w);
+  fetch(rs + grp, re);
   for (int r = item.x; r < item.y; r++) {
-    const int64_t rs = max(a.rowptr[r], item.z), re = min(a.rowptr[r + 1], item.w);
+    const int64_t re2 = r + 1 < item.y ? min(a.rowptr[r + 2], item.w) : re;
     floatx4 acc[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; v++) acc[v] = floatx4{0, 0, 0, 0};
-    int64_t jj = rs + grp;
-    for (; jj + (UNR - 1) * NPAR < re; jj += UNR * NPAR) {
-      int32_t cc[UNR];
-      float vv[UNR];
+    if (rs == re) fetch(re + grp, re2);
+    while (rs < re) {
+      floatx4 x[UNR][VPL];
+      float w[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; u++) {
-        cc[u] = a.col[jj + u * NPAR];
-        vv[u] = ld_val<TV>(a.val, jj + u * NPAR);
+        w[u] = vv[u];
+#pragma unroll
+        for (int v = 0; v < VPL; v++)
+          x[u][v] = cc[u] >= 0 ? ld_x4<TX, VEC>(X + (int64_t)cc[u] * a.ldx, 4 * (q + LPN * v), K)
+                               : floatx4{0, 0, 0, 0};
       }
-      floatx4 x[UNR][VPL];
+      rs += UNR * NPAR;
+      if (rs < re) fetch(rs + grp, re);
+      else fetch(re + grp, re2);
 #pragma unroll
       for (int u = 0; u < UNR; u++)
 #pragma unroll
-        for (int v = 0; v < VPL; v++) x[u][v] = ld_x4<TX, VEC>(X + (int64_t)cc[u] * a.ldx, 4 * (q + LPN * v), K);
-#pragma unroll
-      for (int u = 0; u < UNR; u++)
-#pragma unroll
-        for (int v = 0; v < VPL; v++) acc[v] += vv[u] * x[u][v];
+        for (int v = 0; v < VPL; v++) acc[v] += w[u] * x[u][v];
     }
-    for (; jj < re; jj += NPAR) {
-      const int32_t cc = a.col[jj];
-      const float vv = ld_val<TV>(a.val, jj);
-#pragma unroll
-      for (int v = 0; v < VPL; v++) acc[v] += vv * ld_x4<TX, VEC>(X + (int64_t)cc * a.ldx, 4 * (q + LPN * v), K);
-    }
+    rs = re;
+    re = re2;
     // combine the NPAR lane groups (fixed butterfly order)
 #pragma unroll
     for (int off = LPN; off < 64; off <<= 1)
@@ -179,12 +214,7 @@ __device__ __forceinline__ void items_wave(const SpmmKArgs& a, const int4 item, 
     float* dst = slot >= 0 ? a.carry + (int64_t)slot * K : a.out + (int64_t)r * a.ldo;
     if (grp == 0) {
 #pragma unroll
-      for (int v = 0; v < VPL; v++) {
-        const int cb = 4 * (q + LPN * v);
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (cb + e < K) dst[cb + e] = acc[v][e];
-      }
+      for (int v = 0; v < VPL; v++) st_x4(dst, 4 * (q + LPN * v), K, VEC, acc[v]);
     }
   }
 }
@@ -250,13 +280,7 @@ __device__ __forceinline__ void flat_wave(const SpmmKArgs& a, const int4 item, c
       const int cb = EPL * (lane + 64 * v);
 #pragma unroll
       for (int q = 0; q < NQ; q++) {
-        if constexpr (VEC) {
-          if (cb < K) *(floatx4*)(dst + cb + 4 * q) = acc[v * NQ + q];
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; e++)
-            if (cb + e < K) dst[cb + e] = acc[v * NQ + q][e];
-        }
+        st_x4(dst, cb + 4 * q, K, VEC, acc[v * NQ + q]);
         acc[v * NQ + q] = floatx4{0, 0, 0, 0};
       }
     }
@@ -341,18 +365,14 @@ __global__ __launch_bounds__(kFixThreads) void spmm_fixup(const int32_t* __restr
   const int S = kFixThreads / nv > 0 ? kFixThreads / nv : 1;
   const int t = threadIdx.x;
   const int v = t % nv, sl = t / nv;
-  const bool vec = (K % 4) == 0;
+  const bool vec = K >= 4;
   for (int64_t i = blockIdx.x; i < n_fix; i += gridDim.x) {
     const int64_t r = fix[3 * i], first = fix[3 * i + 1], cnt = fix[3 * i + 2];
     floatx4 acc = floatx4{0, 0, 0, 0};
     if (sl < S && t < nv * S) {
       auto seg = [&](int64_t g) -> floatx4 {
-        const float* p = carry + (first + g) * K + 4 * v;
-        if (vec) return *(const floatx4*)p;
-        floatx4 x;
-#pragma unroll
-        for (int e = 0; e < 4; e++) x[e] = 4 * v + e < K ? p[e] : 0.0f;
-        return x;
+        const float* p = carry + (first + g) * K;
+        return vec ? ld_x4<float, true>(p, 4 * v, K) : ld_x4<float, false>(p, 4 * v, K);
       };
       int64_t g = sl;
       for (; g + 3 * S < cnt; g += 4 * S) {
@@ -369,14 +389,7 @@ __global__ __launch_bounds__(kFixThreads) void spmm_fixup(const int32_t* __restr
     if (sl == 0 && t < nv) {
       floatx4 tot = part[v];
       for (int k = 1; k < S; k++) tot += part[k * nv + v];
-      float* dst = out + r * ldo + 4 * v;
-      if (vec) {
-        *(floatx4*)dst = tot;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (4 * v + e < K) dst[e] = tot[e];
-      }
+      st_x4(out + r * ldo, 4 * v, K, vec, tot);
     }
     __syncthreads();  // `part` is written again for the next row
   }
@@ -387,25 +400,25 @@ unsigned blocks_of(const SpmmKArgs& a) {
   return (unsigned)(((a.n_rows + a.group_rows - 1) / a.group_rows + a.seg_waves + 3) / 4);
 }
 
-// only FP32 products go without a host plan
-template <typename TX>
-constexpr bool unplanned_used() {
-  return sizeof(TX) == 4;
-}
-
+// FP32 products: 16-byte rows at every rank but 1 .. 3 (LPN 1); only these go
+// without a host plan
 template <int VPL, int LPN, typename TV, typename TX>
 hipError_t launch_t(const SpmmKArgs& a, bool vec, hipStream_t s) {
   const unsigned blocks = blocks_of(a);
   if (blocks == 0) return hipSuccess;
-  if constexpr (unplanned_used<TX>()) {
-    if (a.n_rows > 0) {
-      if (vec) spmm_items<VPL, LPN, TV, TX, true, false><<<blocks, 256, 0, s>>>(a);
-      else spmm_items<VPL, LPN, TV, TX, false, false><<<blocks, 256, 0, s>>>(a);
-      return hipGetLastError();
+  if constexpr (sizeof(TX) == 4) {
+    if (LPN == 1 && !vec) {
+      if (a.n_rows > 0) spmm_items<1, 1, TV, TX, false, false><<<blocks, 256, 0, s>>>(a);
+      else spmm_items<1, 1, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
+    } else if (a.n_rows > 0) {
+      spmm_items<VPL, LPN, TV, TX, true, false><<<blocks, 256, 0, s>>>(a);
+    } else {
+      spmm_items<VPL, LPN, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
     }
+  } else {
+    if (vec) spmm_items<VPL, LPN, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
+    else spmm_items<VPL, LPN, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
   }
-  if (vec) spmm_items<VPL, LPN, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
-  else spmm_items<VPL, LPN, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -413,15 +426,13 @@ template <int VPL, typename TV, typename TX>
 hipError_t launch_f(const SpmmKArgs& a, bool vec, hipStream_t s) {
   const unsigned blocks = blocks_of(a);
   if (blocks == 0) return hipSuccess;
-  if constexpr (unplanned_used<TX>()) {
-    if (a.n_rows > 0) {
-      if (vec) spmm_flat<VPL, TV, TX, true, false><<<blocks, 256, 0, s>>>(a);
-      else spmm_flat<VPL, TV, TX, false, false><<<blocks, 256, 0, s>>>(a);
-      return hipGetLastError();
-    }
+  if constexpr (sizeof(TX) == 4) {
+    if (a.n_rows > 0) spmm_flat<VPL, TV, TX, true, false><<<blocks, 256, 0, s>>>(a);
+    else spmm_flat<VPL, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
+  } else {
+    if (vec) spmm_flat<VPL, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
+    else spmm_flat<VPL, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
   }
-  if (vec) spmm_flat<VPL, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
-  else spmm_flat<VPL, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -475,6 +486,9 @@ hipError_t spmm_build(SpmmPlan* p, hipStream_t s, const uint8_t* skip) {
   std::vector<int4> items;
   std::vector<int32_t> slot, fix;
   int32_t nseg = 0;
+  // short rows share an item of up to G nonzeros: L of them, or fewer where that
+  // would leave less than four waves to a SIMD (a row's sums don't depend on it)
+  const int64_t G = std::max<int64_t>(32, std::min<int64_t>(L, p->nnz / 4096));
   int64_t r = 0;
   while (r < rows) {
     const int64_t len = (int64_t)rp[r + 1] - rp[r];
@@ -499,7 +513,7 @@ hipError_t spmm_build(SpmmPlan* p, hipStream_t s, const uint8_t* skip) {
     }
     const int64_t r0 = r, j0 = rp[r];
     while (r < rows && r - r0 < kMaxRowsPerItem && (int64_t)rp[r + 1] - rp[r] <= L &&
-           (int64_t)rp[r + 1] - j0 <= L)
+           (r == r0 || (int64_t)rp[r + 1] - j0 <= G))
       r++;
     items.push_back(make_int4((int)r0, (int)r, (int)j0, (int)rp[r]));
     slot.push_back(-1);
@@ -546,9 +560,7 @@ hipError_t spmm_slice(const SpmmPlan& p, Elem t, const void* X0, int64_t ldx, in
   a.carry = p.carry;
   a.n_items = p.n_items;
   a.K = K;
-  const bool vec = (K % 4 == 0) && (ldx % 4 == 0) && (ldo % 4 == 0) &&
-                   (((uintptr_t)X) % (4 * esz) == 0) && ((uintptr_t)out % 16 == 0) &&
-                   ((uintptr_t)p.carry % 16 == 0);
+  const bool vec = t == Elem::F32 ? K >= 4 : K % 4 == 0 && ldx % 4 == 0 && (uintptr_t)X % 8 == 0;
   const bool vec8 = vec && K % 8 == 0 && ldx % 8 == 0 && ((uintptr_t)X) % 16 == 0;
   const bool flat = p.L <= kFlatMaxNnz;  // the flat kernel holds a whole item in registers
   hipError_t e = t == Elem::F32 ? launch_k<float, float>(a, vec, vec8, flat, s)
@@ -588,9 +600,7 @@ hipError_t spmm_unplanned(const SpmmPlan& p, const int32_t* counts, const float*
   a.seg_waves = (int)std::min<int64_t>(2 * most, 4096);
   a.n_seg = counts;
   a.K = K;
-  const bool vec = K % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)out % 16 == 0 &&
-                   (uintptr_t)p.carry % 16 == 0;
-  hipError_t e = launch_k<float, float>(a, vec, false, true, s);
+  hipError_t e = launch_k<float, float>(a, K >= 4, false, true, s);
   if (e != hipSuccess || most == 0) return e;
   spmm_fixup<<<(unsigned)std::min<int64_t>(most, 512), kFixThreads, 0, s>>>(p.fix, 0, counts + 1, p.carry,
                                                                           out, K, K);
