@@ -95,19 +95,22 @@ def load_workload(name, K, precision):
 def step_work(step, V, D, K, nnz, dense=False, precision="fp32"):
     """Algorithmic work of one launch of a step: (amount, unit, bound, peak).
 
-    Column updates and Grams: 2 rows K^2 flop on the FP32 matrix cores.
-    Dense products: 2 V D K flop on the matrix cores of their input type.
+    Column updates and Grams: 2 rows K^2 flop on the FP32 matrix cores; from
+    65,536 rows on (Grams, H) as six products of BF16 parts.
+    Dense products: 2 V D K flop on the BF16 matrix cores, for FP32 inputs as
+    six products of BF16 parts.
     Sparse products: compulsory bytes -- the CSR (index and value per nonzero,
     row pointers), the gathered factor read once and the output written once."""
     if step == "update_W":
         return 2.0 * V * K * K, "flop", "mfma", PEAK["fp32_tflops"]
+    split = PEAK["bf16_tflops"] / 6
     if step == "update_H":
-        return 2.0 * D * K * K, "flop", "mfma", PEAK["fp32_tflops"]
+        return 2.0 * D * K * K, "flop", "mfma", split if D >= 65536 else PEAK["fp32_tflops"]
     if step in ("gram_S", "gram_Q"):
         rows = V if step == "gram_S" else D
-        return 2.0 * rows * K * K, "flop", "mfma", PEAK["fp32_tflops"]
+        return 2.0 * rows * K * K, "flop", "mfma", split if rows >= 65536 else PEAK["fp32_tflops"]
     if dense:
-        peak = PEAK["bf16_tflops"] if precision == "bf16" else PEAK["fp32_tflops"]
+        peak = PEAK["bf16_tflops"] if precision == "bf16" else split
         return 2.0 * V * D * K, "flop", "mfma", peak
     rows_out, rows_x = (D, V) if step == "product_R" else (V, D)
     vbytes = 6.0 if precision == "bf16" else 8.0

@@ -1706,9 +1706,10 @@ int hals_rows_per_group_h() { return kRowsH; }
 // LDS-resident kernel (32 rows per workgroup) keeps more CUs busy, as long as
 // all its workgroups are resident at once; once they need a second round (its
 // LDS holds two workgroups per CU up to K = 224, one above), the rows kernel's
-// single round is shorter.  Measured on 11,000 rows: K = 200 LDS 38 us, rows
-// 64 us; K = 240 LDS 96 us, rows 76 us; K = 400 LDS 220 us, rows 161 us; on
-// 10,000 rows at K = 240: LDS 111 us, rows 79 us.
+// single round is no longer than two.  Measured (LDS / rows, us): K = 200, 10,000
+// rows 39 / 58, 16,000 rows 40 / 59, 20,000 rows 64 / 60; K = 240, 8,192 rows
+// 38 / 69, 10,000 rows 70 / 70, 20,000 rows 104 / 71; K = 400, 8,192 rows 84 / 140,
+// 10,000 rows 156 / 141.
 // NMF_H_KERNEL=rows|lds forces one (read when the half starts: measurement,
 // tests).
 static bool h_rows_kernel_for(int64_t rows, int K, int cus) {
