@@ -68,7 +68,9 @@ typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
 // lane takes columns K-4..K-1 and repeats sums of its neighbour's: the same
 // loads in the same order, so both write the same bits.  On 6,037 x 2,741
 // with 165,000 nonzeros at K = 77 (both products): 65 us with scalar loads, 43 so.
-// BF16: K % 4 == 0 and 8-byte alignment.
+// BF16: K % 4 == 0 and aligned rows; the flat kernel stores its sums where they are
+// (the moved column costs the packed form eight registers, a wave per SIMD and 8% at
+// K = 400).
 __device__ __forceinline__ void st_x4(float* row, int c, int K, bool vec, floatx4 v) {
   if (vec) {
     if (c < K) *(any4*)(row + min(c, K - 4)) = v;
@@ -280,7 +282,11 @@ __device__ __forceinline__ void flat_wave(const SpmmKArgs& a, const int4 item, c
       const int cb = EPL * (lane + 64 * v);
 #pragma unroll
       for (int q = 0; q < NQ; q++) {
-        st_x4(dst, cb + 4 * q, K, VEC, acc[v * NQ + q]);
+        if constexpr (VEC && sizeof(TX) == 2) {
+          if (cb < K) *(floatx4*)(dst + cb + 4 * q) = acc[v * NQ + q];
+        } else {
+          st_x4(dst, cb + 4 * q, K, VEC, acc[v * NQ + q]);
+        }
         acc[v * NQ + q] = floatx4{0, 0, 0, 0};
       }
     }
@@ -560,7 +566,9 @@ hipError_t spmm_slice(const SpmmPlan& p, Elem t, const void* X0, int64_t ldx, in
   a.carry = p.carry;
   a.n_items = p.n_items;
   a.K = K;
-  const bool vec = t == Elem::F32 ? K >= 4 : K % 4 == 0 && ldx % 4 == 0 && (uintptr_t)X % 8 == 0;
+  const bool vec = t == Elem::F32 ? K >= 4 : K % 4 == 0 && ldx % 4 == 0 && ldo % 4 == 0 &&
+                                                (uintptr_t)X % 8 == 0 && (uintptr_t)out % 16 == 0 &&
+                                                (uintptr_t)p.carry % 16 == 0;
   const bool vec8 = vec && K % 8 == 0 && ldx % 8 == 0 && ((uintptr_t)X) % 16 == 0;
   const bool flat = p.L <= kFlatMaxNnz;  // the flat kernel holds a whole item in registers
   hipError_t e = t == Elem::F32 ? launch_k<float, float>(a, vec, vec8, flat, s)
