@@ -30,6 +30,7 @@ struct FoldWs {
   float* partial;
   float* gpart;   // Gram partials
   float* panel;   // tile panels of the H update
+  size_t panel_floats;
   double* red;
   double* scal;   // [0] a2 [3] half [4] rel, then the counters
   double* trace;  // [kTraceChunk]
@@ -47,7 +48,10 @@ struct FoldWs {
   int L;
 };
 
-FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* AnewT, int hidden) {
+// `least`: the least workspace a fold-in can do with (R' of dense documents without
+// splits), for the library's own array, which has a fixed size.
+FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* AnewT, int hidden,
+                   bool least) {
   Carver c(base);
   FoldWs f{};
   f.R = c.take<float>((size_t)(Dn * K));
@@ -55,13 +59,14 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
   f.Qn = c.take<float>((size_t)K * K);
   size_t part = 1;
   if (AnewT->format == NMF_DENSE) {
-    const int sp = gemm_plan(Elem::F32, Dn, K, V).splits;
+    const int sp = gemm_plan(Elem::F32, Dn, K, V, least ? 1 : 256).splits;
     if (sp > 1) part = std::max(part, (size_t)sp * Dn * K);
   }
   f.partial = c.take<float>(part);
   f.gpart = c.take<float>(gram_partial_floats(K));
-  f.panel = c.take<float>(std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),
-                                    hals_panel_floats(K, 64)));
+  f.panel_floats = std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),
+                            hals_panel_floats(K, 64));
+  f.panel = c.take<float>(f.panel_floats);
   f.red = c.take<double>(kObjParts);
   f.scal = c.take<double>(8 + 2);
   f.counter = (int32_t*)(f.scal + 8);
@@ -124,7 +129,7 @@ int nmf_foldin_workspace_bytes(nmf_plan p, const nmf_matrix* AnewT, int mlp_hidd
   if (!p || !bytes) return fail(NMF_E_ARG, "NULL argument");
   int rc = check_anew(p, AnewT);
   if (rc) return rc;
-  *bytes = fold_layout(nullptr, AnewT->rows, p->V, p->K, AnewT, mlp_hidden).off;
+  *bytes = fold_layout(nullptr, AnewT->rows, p->V, p->K, AnewT, mlp_hidden, false).off;
   return NMF_OK;
 }
 
@@ -132,17 +137,24 @@ int nmf_foldin(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int init_mode
                const void* mlp_params, int mlp_hidden, int max_sweeps, double tol,
                int* sweeps_done, double* rel_trace, void* workspace, size_t workspace_bytes) {
   return foldin_run(p, AnewT, Ht_new, init_mode, mlp_params, mlp_hidden, max_sweeps, tol,
-                    sweeps_done, rel_trace, workspace, workspace_bytes);
+                    sweeps_done, rel_trace, workspace, workspace_bytes, false);
 }
 
 }  // extern "C"
+
+int plnmf::foldin_least_bytes(nmf_plan p, const nmf_matrix* AnewT, int hidden, size_t* bytes) {
+  int rc = check_anew(p, AnewT);
+  if (rc) return rc;
+  *bytes = fold_layout(nullptr, AnewT->rows, p->V, p->K, AnewT, hidden, true).off;
+  return NMF_OK;
+}
 
 // The body of nmf_foldin, shared with the entry point whose workspace is the
 // library's own device array.
 int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int init_mode,
                       const void* mlp_params, int mlp_hidden, int max_sweeps, double tol,
                       int* sweeps_done, double* rel_trace, void* workspace,
-                      size_t workspace_bytes) {
+                      size_t workspace_bytes, bool least) {
   if (sweeps_done) *sweeps_done = 0;
   if (!p || !Ht_new || !workspace) return fail(NMF_E_ARG, "NULL argument");
   if (!(tol >= 0.0) || std::isinf(tol)) return fail(NMF_E_ARG, "tol must be finite and >= 0");
@@ -160,7 +172,7 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
   const int64_t Dn = AnewT->rows;
   const int K = p->K;
   const int hid = init_mode == NMF_FOLDIN_MLP ? mlp_hidden : 0;
-  FoldWs f = fold_layout(workspace, Dn, p->V, K, AnewT, hid);
+  FoldWs f = fold_layout(workspace, Dn, p->V, K, AnewT, hid, least);
   if (workspace_bytes < f.off)
     return fail(NMF_E_WORKSPACE, "fold-in workspace %zu < %zu", workspace_bytes, f.off);
   hipStream_t s = p->stream;
@@ -208,7 +220,7 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
     g.C = f.R;
     g.ldc = K;
     g.epi = EPI_STORE;
-    gemm_use(g, gemm_plan(Elem::F32, g.M, g.N, g.Kd));
+    gemm_use(g, gemm_plan(Elem::F32, g.M, g.N, g.Kd, least ? 1 : 256));
     g.partial = f.partial;
     FCHECK(gemm(Elem::F32, false, false, g, s));
     if (objective) {
@@ -217,9 +229,7 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
       FCHECK(finish_f64(f.red, nb, f.scal + 0, s));
     }
   }
-  FCHECK(hipMemsetAsync(f.panel, 0,
-                        std::max(std::max(hals_panel_floats(K, 16), hals_panel_floats(K, 32)),
-                                 hals_panel_floats(K, 64)) * sizeof(float), s));
+  FCHECK(hipMemsetAsync(f.panel, 0, f.panel_floats * sizeof(float), s));
   const int order = hals_h_order(Dn, K, p->cus, p->h_tile);
   FCHECK(gram_with(p->W, p->V, K, f.S, f.gpart, p->cus, s, f.panel, p->h_tile, order));
 

@@ -46,6 +46,9 @@ extern "C" int nmf_foldin_noalloc(nmf_plan p, const nmf_matrix* AnewT, float* Ht
   const int hid = init_mode == NMF_FOLDIN_MLP ? mlp_hidden : 0;
   int rc = nmf_foldin_workspace_bytes(p, AnewT, hid, &need);
   if (rc) return rc;
+  const bool least = need > (size_t)NMF_NOALLOC_SCRATCH_BYTES;
+  if (least) rc = foldin_least_bytes(p, AnewT, hid, &need);
+  if (rc) return rc;
   if (need > (size_t)NMF_NOALLOC_SCRATCH_BYTES)
     return fail(NMF_E_WORKSPACE,
                 "fold-in of %lld documents needs %zu bytes of workspace, more than the "
@@ -60,5 +63,5 @@ extern "C" int nmf_foldin_noalloc(nmf_plan p, const nmf_matrix* AnewT, float* Ht
   rc = scratch_address(dev, &ptr);
   if (rc) return rc;
   return foldin_run(p, AnewT, Ht_new, init_mode, mlp_params, mlp_hidden, max_sweeps, tol,
-                    sweeps_done, rel_trace, ptr, (size_t)NMF_NOALLOC_SCRATCH_BYTES);
+                    sweeps_done, rel_trace, ptr, (size_t)NMF_NOALLOC_SCRATCH_BYTES, least);
 }

@@ -119,5 +119,7 @@ int enqueue_objective(nmf_plan_s* p);
 // nmf_foldin on a given workspace (also serves the entry point that brings none)
 int foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int init_mode,
                const void* mlp_params, int mlp_hidden, int max_sweeps, double tol,
-               int* sweeps_done, double* rel_trace, void* workspace, size_t workspace_bytes);
+               int* sweeps_done, double* rel_trace, void* workspace, size_t workspace_bytes,
+               bool least);
+int foldin_least_bytes(nmf_plan p, const nmf_matrix* AnewT, int hidden, size_t* bytes);
 }  // namespace plnmf
