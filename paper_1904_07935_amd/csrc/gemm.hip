@@ -578,21 +578,28 @@ hipError_t launch(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, bool AT, bool BT>
-hipError_t launch_form(const GemmArgs& g, bool far, int cfg, hipStream_t s) {
+// The form launched is the form set in `g`, however the operands are loaded:
+// the caller sizes and adds the tiles' sums (red_out, col_part) by it.
+template <typename T, bool AT, bool BT, bool FAR>
+hipError_t launch_form(const GemmArgs& g, hipStream_t s) {
   if (!epi_used<T, AT, BT>(g.epi)) return hipErrorInvalidValue;
-  if (far) return cfg == 0 ? launch<T, AT, BT, true, 0>(g, s) : launch<T, AT, BT, true, 1>(g, s);
-  switch (cfg) {
-    case 0: return launch<T, AT, BT, false, 0>(g, s);
-    case 1: return launch<T, AT, BT, false, 1>(g, s);
-    default: return launch<T, AT, BT, false, 2>(g, s);
+  switch (g.cfg) {
+    case 0: return launch<T, AT, BT, FAR, 0>(g, s);
+    case 1: return launch<T, AT, BT, FAR, 1>(g, s);
+    case 2: return launch<T, AT, BT, FAR, 2>(g, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
+template <typename T, bool FAR>
+hipError_t launch_elem(bool a_trans, bool b_trans, const GemmArgs& g, hipStream_t s) {
+  if (a_trans) return b_trans ? hipErrorInvalidValue : launch_form<T, true, false, FAR>(g, s);
+  return b_trans ? launch_form<T, false, true, FAR>(g, s) : launch_form<T, false, false, FAR>(g, s);
+}
+
 template <typename T>
-hipError_t launch_elem(bool a_trans, bool b_trans, const GemmArgs& g, bool far, int cfg, hipStream_t s) {
-  if (a_trans) return b_trans ? hipErrorInvalidValue : launch_form<T, true, false>(g, far, cfg, s);
-  return b_trans ? launch_form<T, false, true>(g, far, cfg, s) : launch_form<T, false, false>(g, far, cfg, s);
+hipError_t launch_type(bool a_trans, bool b_trans, const GemmArgs& g, bool far, hipStream_t s) {
+  return far ? launch_elem<T, true>(a_trans, b_trans, g, s) : launch_elem<T, false>(a_trans, b_trans, g, s);
 }
 
 struct CfgCost {
@@ -665,14 +672,13 @@ hipError_t splitk_reduce(const float* partial, int splits, int64_t M, int64_t N,
 
 hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  if (g.cfg < 0 || g.cfg > 2) return hipErrorInvalidValue;
   if (g.epi == EPI_RESID_SQ && g.cfg != 0) return hipErrorInvalidValue;
   // dword-aligned rows within 32-bit tile offsets; else element by element
   const size_t es = t == Elem::F32 ? 4 : 2;
   const bool far = !aligned(g.A, 4) || !aligned(g.B, 4) || (g.lda * es) % 4 || (g.ldb * es) % 4 ||
                    g.lda >= (int64_t(1) << 22) || g.ldb >= (int64_t(1) << 22);
-  const hipError_t e = t == Elem::F32 ? launch_elem<float>(a_trans, b_trans, g, far, g.cfg, s)
-                                      : launch_elem<__bf16>(a_trans, b_trans, g, far, g.cfg, s);
+  const hipError_t e = t == Elem::F32 ? launch_type<float>(a_trans, b_trans, g, far, s)
+                                      : launch_type<__bf16>(a_trans, b_trans, g, far, s);
   if (e != hipSuccess) return e;
   if (g.splits > 1 && g.epi == EPI_STORE && g.C)  // without C the caller sums the partials
     return splitk_reduce(g.partial, g.splits, g.M, g.N, g.C, g.ldc, g.bias, s);
