@@ -9,9 +9,10 @@
 // three BF16 parts that add up to it exactly (8 + 8 + 8 significand bits), and
 // a product x y is the sum of the six part products of order 2^-16 and above:
 // xh yh + (xh ym + xm yh) + (xh yl + xm ym + xl yh).  What is left out, xm yl +
-// xl ym + xl yl, is at most a few units of 2^-24 of the product and of either
-// sign, like one FP32 rounding.  Six v_mfma_f32_32x32x16_bf16 cover 16 terms in
-// 192 cycles per 32 x 32 block; eight v_mfma_f32_32x32x2_f32 take 512.
+// xl ym + xl yl, is at most 2^-24 of the product and of either sign (RMS 5.3e-9;
+// an FP32 rounding is at most 2^-24, RMS 2.5e-8).  Six v_mfma_f32_32x32x16_bf16
+// cover 16 terms in 192 cycles per 32 x 32 block; eight v_mfma_f32_32x32x2_f32
+// take 512.
 //
 // One operand layout serves both element types: lane l of the 32x32x16 product
 // supplies A[l%32][8(l/32)..+7] and B[8(l/32)..+7][l%32], so a tile is staged in
@@ -324,16 +325,21 @@ __device__ __forceinline__ void tile_of(int& tx, int& ty, int& tz) {
   tz = (int)(t / (gx * gy));
 }
 
-// Main loop: double-buffered LDS; the loads of a later step are issued before
-// a step's products and stored (split) to the other buffer after them.  FP32
-// prefetches one step ahead (a step's products take longer than a load), BF16
-// two.
+// Main loop.  One LDS buffer (128 x 128 and 64 x 64): the next step's loads are
+// issued before a step's products and stored (split) after the barrier that
+// follows them.  Two buffers (128 x 32): the step after goes to the other buffer,
+// and BF16, whose products take less time than a load, loads two steps ahead.
 //
-// FP32: two-level accumulation.  Each step's 32 terms go into a fresh
-// accumulator, the small part products before the high ones, which is then
-// added to the running total: a single chain over n terms carries a rounding
-// error that grows like the square root of its length, and within a step only
-// two additions happen at the sum's full size.
+// FP32: the matrix core adds the products of eight terms, cut to 2^-23 of the
+// largest, and rounds the sum into the accumulator; an accumulator smaller than
+// the sum is cut.  So the high products and the small ones (2^-8 of them and less)
+// have accumulators of their own.  The small ones' runs through the whole
+// contraction and is added at the end: its roundings are 2^-8 of the others'.  The
+// high ones' takes a step's 32 terms and is then added to the running total: a
+// single chain over n terms carries a rounding error that grows like the square
+// root of its length.  Single products are off by 2.6e-8 (RMS) and 1.0e-7 at most;
+// with one accumulator for both it was 4.1e-8 and 2.9e-7, on the FP32 matrix cores
+// 2.5e-8 and 6e-8.
 // BF16: one chain.  The inputs' rounding (2^-9 relative) dwarfs the FP32
 // chain's, and at BF16 rates the chunk additions would cost as much VALU time
 // as the products take on the matrix cores.
@@ -343,7 +349,7 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
   constexpr int BM = Tl::BM, BN = Tl::BN, BI = Tl::BI, BJ = Tl::BJ, BK = bk_of<T, CFG>();
   constexpr int NTHR = threads_of<CFG>(), NWN = BN / (32 * BJ), K8 = BK / 8, PL = parts_of<T>();
   constexpr bool F32 = sizeof(T) == 4;
-  constexpr int NB = Tl::BUFS, DIST = F32 || NB == 1 ? 1 : 2, STEPS = 2;
+  constexpr int NB = Tl::BUFS, DIST = F32 || FAR || NB == 1 ? 1 : 2, STEPS = 2;
   using SA = Stage<T, AT, FAR, BM, BK, NTHR>;
   using SB = Stage<T, !BT, FAR, BN, BK, NTHR>;
   constexpr int RPA = SA::RP, RPB = SB::RP, ABUF = PL * K8 * RPA, BUF = ABUF + PL * K8 * RPB;
@@ -373,6 +379,16 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
 #pragma unroll
       for (int e = 0; e < 16; e++) tot[i][j][e] = 0.0f;
 
+  floatx16 lo[F32 ? BI : 1][F32 ? BJ : 1];
+  if constexpr (F32) {
+#pragma unroll
+    for (int i = 0; i < BI; i++)
+#pragma unroll
+      for (int j = 0; j < BJ; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) lo[i][j][e] = 0.0f;
+  }
+
   SA sa[DIST];
   SB sb[DIST];
 #pragma unroll
@@ -389,54 +405,82 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
     sa[s].store(lds + b * BUF, tid);
     sb[s].store(lds + b * BUF + ABUF, tid);
   };
-  auto products = [&](int b, floatx16(&acc)[BI][BJ]) {
+  auto products = [&](int b) {
     const uintx4* la = lds + b * BUF + (lane >> 5) * RPA + wm * 32 * BI + (lane & 31);
     const uintx4* lb = lds + b * BUF + ABUF + (lane >> 5) * RPB + wn * 32 * BJ + (lane & 31);
-#pragma unroll
-    for (int s = 0; s < BK / 16; s++) {
-      bf16x8 a[PL][BI], c[PL][BJ];
-#pragma unroll
-      for (int p = PL - 1; p >= 0; p--) {
-#pragma unroll
-        for (int i = 0; i < BI; i++)
-          a[p][i] = __builtin_bit_cast(bf16x8, la[(p * K8 + 2 * s) * RPA + 32 * i]);
-#pragma unroll
-        for (int j = 0; j < BJ; j++)
-          c[p][j] = __builtin_bit_cast(bf16x8, lb[(p * K8 + 2 * s) * RPB + 32 * j]);
-      }
-      auto mul = [&](int p, int q) {
-#pragma unroll
-        for (int i = 0; i < BI; i++)
-#pragma unroll
-          for (int j = 0; j < BJ; j++)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p][i], c[q][j], acc[i][j], 0, 0, 0);
-      };
-      if constexpr (F32) {
-        mul(2, 0);
-        mul(0, 2);
-        mul(1, 1);
-        mul(1, 0);
-        mul(0, 1);
-        // the high parts last, so that the small products are added to a sum
-        // that is still small: the last 16 terms' now, the others' below
-        if (s == BK / 16 - 1) mul(0, 0);
-      } else {
-        mul(0, 0);
-      }
-    }
+    auto read_a = [&](int s, int p, int i) {
+      return __builtin_bit_cast(bf16x8, la[(p * K8 + 2 * s) * RPA + 32 * i]);
+    };
+    auto read_b = [&](int s, int p, int j) {
+      return __builtin_bit_cast(bf16x8, lb[(p * K8 + 2 * s) * RPB + 32 * j]);
+    };
+    auto mul = [](bf16x8 x, bf16x8 y, floatx16& c) {
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0);
+    };
     if constexpr (F32) {
+      // One block after the other, its products in the order high, middle and low
+      // part of B; each part is read during the products of the part before.
+      constexpr int S = BK / 16;
+      bf16x8 a[3][S], c[3][S];
+      auto load_a = [&](int p, int i) {
 #pragma unroll
-      for (int s = 0; s < BK / 16 - 1; s++) {
+        for (int s = 0; s < S; s++) a[p][s] = read_a(s, p, i);
+      };
+      auto load_b = [&](int p, int j) {
+#pragma unroll
+        for (int s = 0; s < S; s++) c[p][s] = read_b(s, p, j);
+      };
+      load_a(0, 0);
+      load_b(0, 0);
+      load_a(2, 0);
+      load_a(1, 0);
+#pragma unroll
+      for (int i = 0; i < BI; i++) {
+#pragma unroll
+        for (int j = 0; j < BJ; j++) {
+          const bool last_j = j + 1 == BJ, last = last_j && i + 1 == BI;
+          floatx16 hi;
+#pragma unroll
+          for (int e = 0; e < 16; e++) hi[e] = 0.0f;
+          load_b(1, j);
+#pragma unroll
+          for (int s = 0; s < S; s++) {
+            mul(a[0][s], c[0][s], hi);
+            mul(a[2][s], c[0][s], lo[i][j]);
+            mul(a[1][s], c[0][s], lo[i][j]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          load_b(2, j);
+          if (last_j && !last) load_a(2, i + 1);
+#pragma unroll
+          for (int s = 0; s < S; s++) {
+            mul(a[0][s], c[1][s], lo[i][j]);
+            mul(a[1][s], c[1][s], lo[i][j]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (!last) load_b(0, last_j ? 0 : j + 1);
+          if (last_j && !last) load_a(1, i + 1);
+#pragma unroll
+          for (int s = 0; s < S; s++) mul(a[0][s], c[2][s], lo[i][j]);
+          tot[i][j] += hi;
+          // added here and now: the next block takes hi's registers
+          asm volatile("" : "+v"(tot[i][j]));
+          if (last_j && !last) load_a(0, i + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < BK / 16; s++) {
         bf16x8 a[BI], c[BJ];
 #pragma unroll
-        for (int i = 0; i < BI; i++) a[i] = __builtin_bit_cast(bf16x8, la[2 * s * RPA + 32 * i]);
+        for (int i = 0; i < BI; i++) a[i] = read_a(s, 0, i);
 #pragma unroll
-        for (int j = 0; j < BJ; j++) c[j] = __builtin_bit_cast(bf16x8, lb[2 * s * RPB + 32 * j]);
+        for (int j = 0; j < BJ; j++) c[j] = read_b(s, 0, j);
 #pragma unroll
         for (int i = 0; i < BI; i++)
 #pragma unroll
-          for (int j = 0; j < BJ; j++)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], c[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < BJ; j++) mul(a[i], c[j], tot[i][j]);
       }
     }
   };
@@ -453,27 +497,19 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
     for (int u = 0; u < STEPS; u++) {
       if (kt + u < nk) {
         if (kt + u + DIST < nk) fetch(u % DIST, kt + u + DIST);
-        if constexpr (F32) {
-          floatx16 acc[BI][BJ];
-#pragma unroll
-          for (int i = 0; i < BI; i++)
-#pragma unroll
-            for (int j = 0; j < BJ; j++)
-#pragma unroll
-              for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
-          products(u % NB, acc);
-#pragma unroll
-          for (int i = 0; i < BI; i++)
-#pragma unroll
-            for (int j = 0; j < BJ; j++) tot[i][j] += acc[i][j];
-        } else {
-          products(u % NB, tot);
-        }
+        products(u % NB);
         if (NB == 1) __syncthreads();
         if (kt + u + 1 < nk) put((u + 1) % DIST, (u + 1) % NB);
         __syncthreads();
       }
     }
+  }
+
+  if constexpr (F32) {
+#pragma unroll
+    for (int i = 0; i < BI; i++)
+#pragma unroll
+      for (int j = 0; j < BJ; j++) tot[i][j] += lo[i][j];
   }
 
   const bool split = splits > 1;
@@ -545,19 +581,18 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ partial, int spli
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t m = i / N, n = i - m * N;
-    float s = 0.0f;
+    double s = 0.0;  // the partials are as large as the sum: one rounding for all
     int z = 0;
     for (; z + 3 < splits; z += 4) {  // four loads in flight, added in split order
       const float a = partial[(int64_t)z * total + i], b = partial[(int64_t)(z + 1) * total + i];
       const float c = partial[(int64_t)(z + 2) * total + i], d = partial[(int64_t)(z + 3) * total + i];
-      s += a;
-      s += b;
-      s += c;
-      s += d;
+      s += (double)a;
+      s += (double)b;
+      s += (double)c;
+      s += (double)d;
     }
-    for (; z < splits; z++) s += partial[(int64_t)z * total + i];
-    if (bias) s += bias[n];
-    C[m * ldc + n] = s;
+    for (; z < splits; z++) s += (double)partial[(int64_t)z * total + i];
+    C[m * ldc + n] = bias ? (float)s + bias[n] : (float)s;
   }
 }
 
