@@ -14,9 +14,14 @@
 //    the first: BF16 matrix cores, every FP32 value split into three BF16 parts
 //    (split8 in bf16x3.hpp), a column split once per stage for all its products.
 //    LDS holds 16-byte chunks of eight consecutive rows of one column,
-//    [part][row/8][column].  Its sums are as accurate (100,000 x 400 and
-//    300,000 x 400: the factors after a half agree with 64 bits as before) but
-//    rounded in another order.  Fewer rows stay with the FP32 chain: there the
+//    [part][row/8][column].  The high products have an accumulator of their own:
+//    beside them the small ones (2^-8 of them and less) are below its rounding
+//    after some hundred rows, and what falls away there is of one sign on the
+//    diagonal.  Up to 256 columns the small ones' accumulator runs along; above,
+//    for want of registers, it takes one stage's and is added.  Error against 64
+//    bits, RMS relative, FP32 kernel / this one: 300,000 x 400 2.4e-7 / 7.8e-8
+//    (one accumulator for both: 1.2e-6), 100,000 x 200 8.8e-8 / 6.6e-8, 65,536 x
+//    40 6.9e-8 / 6.1e-8.  Fewer rows stay with the FP32 chain: there the
 //    launch and the first load take most of the time (6,037 x 77: 8 us FP32;
 //    26,000 x 200: 24 us FP32, 16 us split), and a sweep of a small sparse corpus, whose weak components
 //    amplify the last bit of S and Q some hundredfold, keeps its trajectory.
@@ -212,6 +217,7 @@ __global__ __launch_bounds__(kThreads) void gram_partial_split(const float* __re
   using M = Mode<MODE>;
   constexpr int KS = M::KS, UPW = M::UPW, BK = M::BK, K8 = BK / 8, BUFS = M::BUFS;
   constexpr int UW = kWaves / KS;                             // waves over units
+  constexpr bool KEEP = UPW == 1;  // the small products' sums fit beside the high ones'
   constexpr int NI = (M::COLS * K8 + kThreads - 1) / kThreads;  // items per thread, at most
   extern __shared__ __align__(16) unsigned char gram_lds[];
   uintx4* lds = (uintx4*)gram_lds;
@@ -242,6 +248,15 @@ __global__ __launch_bounds__(kThreads) void gram_partial_split(const float* __re
       for (int j = 0; j < 2; j++)
 #pragma unroll
         for (int e = 0; e < 16; e++) acc[k][i][j][e] = 0.0f;
+  floatx16 lo[KEEP ? 2 : 1][KEEP ? 2 : 1];
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) lo[i][j][e] = 0.0f;
+  }
 
   // item i of a thread: eight rows of one column (column fastest)
   unsigned v[NI][8];
@@ -298,19 +313,37 @@ __global__ __launch_bounds__(kThreads) void gram_partial_split(const float* __re
             a[p][i] = __builtin_bit_cast(bf16x8, base[p * PLANE + 64 * pi[k] + 32 * i]);
             c[p][i] = __builtin_bit_cast(bf16x8, base[p * PLANE + 64 * pj[k] + 32 * i]);
           }
-        auto mul = [&](int p, int q) {
+        auto mul = [&](int p, int q, int i, int j, floatx16& x) {
+          x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p][i], c[q][j], x, 0, 0, 0);
+        };
 #pragma unroll
-          for (int i = 0; i < 2; i++)
+        for (int i = 0; i < 2; i++) {
+          floatx16 t[2];
+          if constexpr (!KEEP) {
 #pragma unroll
             for (int j = 0; j < 2; j++)
-              acc[k][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p][i], c[q][j], acc[k][i][j], 0, 0, 0);
-        };
-        mul(2, 0);
-        mul(0, 2);
-        mul(1, 1);
-        mul(1, 0);
-        mul(0, 1);
-        mul(0, 0);
+#pragma unroll
+              for (int e = 0; e < 16; e++) t[j][e] = 0.0f;
+          }
+#pragma unroll
+          for (int j = 0; j < 2; j++) {
+            floatx16& x = KEEP ? lo[KEEP ? i : 0][KEEP ? j : 0] : t[j];
+            mul(2, 0, i, j, x);
+            mul(0, 2, i, j, x);
+            mul(1, 1, i, j, x);
+            mul(1, 0, i, j, x);
+            mul(0, 1, i, j, x);
+            mul(0, 0, i, j, acc[k][i][j]);
+          }
+          if constexpr (!KEEP) {
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+              acc[k][i][j] += t[j];
+              asm volatile("" : "+v"(acc[k][i][j]));  // added here and now: registers
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
     }
   };
@@ -346,6 +379,12 @@ __global__ __launch_bounds__(kThreads) void gram_partial_split(const float* __re
     }
   }
 
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) acc[0][i][j] += lo[i][j];
+  }
   // lane holds C block row 8 jj + 4 h + ii, column lane % 32, in acc[4 jj + ii]
   const int h = lane >> 5, m = lane & 31;
   auto put_blocks = [&](int k, auto value) {
