@@ -863,7 +863,9 @@ hipError_t h_rows_dispatch(const HalsArgs& b, bool vec, hipStream_t s) {
 // VGPRs for the whole sweep as A operands of v_mfma_f32_16x16x32_bf16: lane (m, g),
 // m = lane % 16, g = lane / 16, holds columns 32 t + 8 g .. + 7 of row m in xa[t].
 // The Gram writes the panels already split, in the order the lanes read them
-// ([part][l / 8][column][l % 8]); a tile's panel is copied into the LDS by
+// ([part][l / 8][column][l % 8]); the high products and the small ones have an
+// accumulator each (an accumulator smaller than the sum added to it is cut by the
+// matrix core); a tile's panel is copied into the LDS by
 // direct global-to-LDS loads while the tile before it is in phase 2.
 //
 // Phase 2 runs on the product's own output layout: lane (n, g) holds columns n
@@ -879,7 +881,9 @@ hipError_t h_rows_dispatch(const HalsArgs& b, bool vec, hipStream_t s) {
 // cycles) and the matrix cores are about equal, then phase 2.  Measured on
 // 300,000 x 400: 1,410 -> 960 us (FP32 rows kernel before); 100,000 x 200: 222 ->
 // 140 us.  Per tile at K = 400, cycles of both waves of a SIMD: product 9,300 (7,900
-// with the panel reads left out), phase 2 5,000, the rest 1,500.
+// with the panel reads left out), phase 2 5,000, the rest 1,500.  Error of an
+// update against 64 bits, Frobenius, rows kernel / this one: 100,000 x 200 1.8e-6 /
+// 6.9e-7, 65,537 x 400 2.5e-6 / 9.3e-7.
 constexpr int kRowsSP = 16, kWavesSP = 8;
 constexpr int kTrP = 36;  // pitch of the transpose rows
 __host__ __device__ constexpr size_t sp_panel_bytes(int NT) { return (size_t)3 * 32 * NT * 32 * 2; }
@@ -1023,8 +1027,8 @@ __global__ __launch_bounds__(64 * kWavesSP, 2) void hals_h_split_kernel(HalsArgs
   for (int j = 0; j < ntiles; j++) {
     const int a0 = j * T, tw = a0 + T < K ? T : K - a0;
     if (j > 0) store_tile(j - 1);
-    floatx4 acc[2];
-    acc[0] = acc[1] = floatx4{0, 0, 0, 0};
+    floatx4 hi[2], lo[2];
+    hi[0] = hi[1] = lo[0] = lo[1] = floatx4{0, 0, 0, 0};
     const uintx4* pl = panel + g * 32 + m;
     // step t's panel parts are read during step t - 1 where the registers allow
     constexpr bool AHEAD = NT <= 13;
@@ -1046,25 +1050,25 @@ __global__ __launch_bounds__(64 * kWavesSP, 2) void hals_h_split_kernel(HalsArgs
         read(t, p[0]);
       }
       const bf16x8(&c)[3][2] = p[AHEAD ? t & 1 : 0];
-      auto mul = [&](int u, int q) {
+      auto mul = [&](int u, int q, floatx4 (&acc)[2]) {
 #pragma unroll
         for (int b = 0; b < 2; b++)
           acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[t][u]), c[q][b], acc[b],
                                                            0, 0, 0);
       };
-      mul(2, 0);  // the small parts first
-      mul(0, 2);
-      mul(1, 1);
-      mul(1, 0);
-      mul(0, 1);
-      mul(0, 0);
+      mul(2, 0, lo);
+      mul(0, 0, hi);
+      mul(0, 2, lo);
+      mul(1, 1, lo);
+      mul(1, 0, lo);
+      mul(0, 1, lo);
     }
     __syncthreads();  // every wave is done with the panel
     float y[2][4];
 #pragma unroll
     for (int b = 0; b < 2; b++)
 #pragma unroll
-      for (int i = 0; i < 4; i++) y[b][i] = acc[b][i] + bt[b][i];
+      for (int i = 0; i < 4; i++) y[b][i] = (hi[b][i] + lo[b][i]) + bt[b][i];
     if (j + 1 < ntiles) {
       stage(j + 1);
       load_bt(a0 + T);
