@@ -325,6 +325,61 @@ __device__ __forceinline__ void tile_of(int& tx, int& ty, int& tz) {
   tz = (int)(t / (gx * gy));
 }
 
+// Whether a wave's sums hold an infinity or a NaN.
+template <int BI, int BJ>
+__device__ __forceinline__ bool any_not_finite(const floatx16 (&x)[BI][BJ]) {
+  float z = 0.0f;
+#pragma unroll
+  for (int i = 0; i < BI; i++)
+#pragma unroll
+    for (int j = 0; j < BJ; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) z = fmaf(x[i][j][e], 0.0f, z);
+  return __any(z != z);
+}
+
+// A wave's products on the FP32 matrix cores, straight from memory.  An operand
+// that is infinite, or above the largest BF16, leaves NaN in the sums of the
+// parts where the values' own products are infinite or large; sums that are not
+// finite are therefore formed again from the values.
+template <bool AT, bool BT, int BI, int BJ>
+__device__ __forceinline__ void whole_products(const float* __restrict__ A, const float* __restrict__ B,
+                                               int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t r0,
+                                               int64_t c0, int64_t kb, int64_t ke, floatx16 (&tot)[BI][BJ]) {
+  const int lane = threadIdx.x & 63, h = lane >> 5, l = lane & 31;
+#pragma unroll
+  for (int i = 0; i < BI; i++)
+#pragma unroll
+    for (int j = 0; j < BJ; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) tot[i][j][e] = 0.0f;
+#pragma unroll 1
+  for (int64_t k0 = kb; k0 < ke; k0 += 8) {
+    float a[4][BI], b[4][BJ];  // one memory round trip for eight terms
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int64_t k = k0 + 2 * q + h;
+#pragma unroll
+      for (int i = 0; i < BI; i++) {
+        const int64_t m = r0 + 32 * i + l;
+        a[q][i] = m < M && k < ke ? (AT ? A[k * lda + m] : A[m * lda + k]) : 0.0f;
+      }
+#pragma unroll
+      for (int j = 0; j < BJ; j++) {
+        const int64_t n = c0 + 32 * j + l;
+        b[q][j] = n < N && k < ke ? (BT ? B[n * ldb + k] : B[k * ldb + n]) : 0.0f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+#pragma unroll
+      for (int i = 0; i < BI; i++)
+#pragma unroll
+        for (int j = 0; j < BJ; j++)
+          tot[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][i], b[q][j], tot[i][j], 0, 0, 0);
+  }
+}
+
 // Main loop.  One LDS buffer (128 x 128 and 64 x 64): the next step's loads are
 // issued before a step's products and stored (split) after the barrier that
 // follows them.  Two buffers (128 x 32): the step after goes to the other buffer,
@@ -510,6 +565,10 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
     for (int i = 0; i < BI; i++)
 #pragma unroll
       for (int j = 0; j < BJ; j++) tot[i][j] += lo[i][j];
+    if (any_not_finite(tot))
+      whole_products<AT, BT, BI, BJ>(A, B, lda, ldb, M, N, m0 + wm * 32 * BI, n0 + wn * 32 * BJ, kb, ke, tot);
+    // results over the operand: every wave has its products
+    if (g.epi == EPI_MU && g.C == (const float*)g.A) __syncthreads();
   }
 
   const bool split = splits > 1;
