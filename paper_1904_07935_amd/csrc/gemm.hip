@@ -338,21 +338,22 @@ __device__ __forceinline__ bool any_not_finite(const floatx16 (&x)[BI][BJ]) {
   return __any(z != z);
 }
 
-// A wave's products on the FP32 matrix cores, straight from memory.  An operand
-// that is infinite, or above the largest BF16, leaves NaN in the sums of the
-// parts where the values' own products are infinite or large; sums that are not
-// finite are therefore formed again from the values.
+// An operand that is infinite, or above the largest BF16, leaves NaN in the sums
+// of the parts where the values' own products are infinite or large.  Sums that are
+// not finite are therefore formed again from the values, on the FP32 matrix cores
+// and straight from memory; the others stay.
 template <bool AT, bool BT, int BI, int BJ>
 __device__ __forceinline__ void whole_products(const float* __restrict__ A, const float* __restrict__ B,
                                                int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t r0,
                                                int64_t c0, int64_t kb, int64_t ke, floatx16 (&tot)[BI][BJ]) {
   const int lane = threadIdx.x & 63, h = lane >> 5, l = lane & 31;
+  floatx16 x[BI][BJ];
 #pragma unroll
   for (int i = 0; i < BI; i++)
 #pragma unroll
     for (int j = 0; j < BJ; j++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) tot[i][j][e] = 0.0f;
+      for (int e = 0; e < 16; e++) x[i][j][e] = 0.0f;
 #pragma unroll 1
   for (int64_t k0 = kb; k0 < ke; k0 += 8) {
     float a[4][BI], b[4][BJ];  // one memory round trip for eight terms
@@ -376,8 +377,15 @@ __device__ __forceinline__ void whole_products(const float* __restrict__ A, cons
       for (int i = 0; i < BI; i++)
 #pragma unroll
         for (int j = 0; j < BJ; j++)
-          tot[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][i], b[q][j], tot[i][j], 0, 0, 0);
+          x[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][i], b[q][j], x[i][j], 0, 0, 0);
   }
+#pragma unroll
+  for (int i = 0; i < BI; i++)
+#pragma unroll
+    for (int j = 0; j < BJ; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++)
+        if (!isfinite(tot[i][j][e])) tot[i][j][e] = x[i][j][e];
 }
 
 // Main loop.  One LDS buffer (128 x 128 and 64 x 64): the next step's loads are
@@ -565,7 +573,7 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
     for (int i = 0; i < BI; i++)
 #pragma unroll
       for (int j = 0; j < BJ; j++) tot[i][j] += lo[i][j];
-    if (any_not_finite(tot))
+    if (any_not_finite(tot))  // rare
       whole_products<AT, BT, BI, BJ>(A, B, lda, ldb, M, N, m0 + wm * 32 * BI, n0 + wn * 32 * BJ, kb, ke, tot);
     // results over the operand: every wave has its products
     if (g.epi == EPI_MU && g.C == (const float*)g.A) __syncthreads();
