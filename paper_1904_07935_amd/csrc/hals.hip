@@ -332,11 +332,13 @@ __device__ __forceinline__ float quad_bcast(float v) {
 // rows g[step][k].
 template <int G>
 __device__ __forceinline__ void phase2_steps(float (&y)[T / 4], const float (&g)[4][T / 4], int q, float eps) {
+  // a finished column keeps its unclipped value (clipped again when it is written)
+  // and takes no part in later steps, whatever their x
   auto step = [&](int s, float v) {
     const float x = fmaxf(eps, v);
-    y[G] = q == s ? x : y[G];
+    if (s < 3) y[G] -= (q > s ? x : 0.0f) * g[s][G];
 #pragma unroll
-    for (int k = G; k < T / 4; k++) y[k] -= x * g[s][k];  // g is 0 for columns <= t
+    for (int k = G + 1; k < T / 4; k++) y[k] -= x * g[s][k];
   };
   step(0, quad_bcast<0>(y[G]));
   step(1, quad_bcast<1>(y[G]));
@@ -499,7 +501,7 @@ __global__ __launch_bounds__(256, 2) void hals_h_kernel(HalsArgs a) {
       phase2<0>(y, g, gq + q * (T / 4), q, tw, eps);
 #pragma unroll
       for (int k = 0; k < T / 4; k++)
-        if (4 * k + q < tw) xs[prow * XP + a0 + 4 * k + q] = y[k];
+        if (4 * k + q < tw) xs[prow * XP + a0 + 4 * k + q] = fmaxf(eps, y[k]);
     } else if (j + 1 < ntiles) {
       // the next tile's panel (bp is free once every wave has its product)
       store_panel<128>(next, K, 0, bp, tid - 128);
