@@ -945,6 +945,66 @@ __device__ __forceinline__ void sp_phase2(float (&y)[2][4], float (&gr)[8][2], c
   }
 }
 
+// Where a row holds an infinity, the sums of the parts hold NaN (an infinity's lower
+// parts are NaN).  Then the sums that are not finite are formed again on the FP32
+// matrix cores from the rows in memory (columns below the tile are the new ones by
+// now) and from the panel's parts, added up.
+__device__ __forceinline__ void sp_whole_products(__amdgpu_buffer_rsrc_t xv, const uintx4* pl, int K8, int K, int NT,
+                                               int m, int g, const float (&bt)[2][4], float (&y)[2][4]) {
+  floatx4 acc[2];
+  acc[0] = acc[1] = floatx4{0, 0, 0, 0};
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last tile's stores
+#pragma unroll 1
+  for (int t = 0; t < NT; t++) {
+    const int c = 32 * t + 8 * g;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; e++)
+      x[e] = c + e < K ? __uint_as_float(ld4(xv, (uint32_t)(m * K + c + e) * 4)) : 0.0f;
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      bf16x8 p[3];
+#pragma unroll
+      for (int q = 0; q < 3; q++) p[q] = __builtin_bit_cast(bf16x8, pl[(q * K8 + 4 * t) * 32 + 16 * b]);
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        const float ph = (float)p[0][e];
+        const float w = isfinite(ph) ? ph + ((float)p[1][e] + (float)p[2][e]) : ph;
+        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], w, acc[b], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; b++)
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      if (!isfinite(y[b][i])) y[b][i] = acc[b][i] + bt[b][i];
+}
+
+// Phase 2 with y as above, for values that may be infinite, to the clipped values.
+// As in the rows kernel an infinite value turns to NaN in its own column and, where
+// that is odd, in the one before.
+__device__ __forceinline__ void sp_phase2_whole(float (&y)[2][4], const float* gl, float eps, int tw) {
+  const int lane = threadIdx.x & 63, m = lane & 15;
+#pragma unroll 1
+  for (int t = 0; t < tw; t++) {
+    float x[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      x[i] = fmaxf(eps, __shfl(t < 16 ? y[0][i] : y[1][i], (lane & 48) | (t & 15)));
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      const int c = 16 * b + m;
+      const float gv = gl[t * T + 16 * b];  // 0 for columns <= t
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const float v = c == t ? x[i] : y[b][i];
+        y[b][i] = c >= (t & ~1) ? v - x[i] * gv : v;
+      }
+    }
+  }
+}
+
 template <int NT, bool VEC>
 __global__ __launch_bounds__(64 * kWavesSP, 2) void hals_h_split_kernel(HalsArgs a) {
   extern __shared__ __align__(16) unsigned char sp_lds[];
@@ -1065,28 +1125,39 @@ __global__ __launch_bounds__(64 * kWavesSP, 2) void hals_h_split_kernel(HalsArgs
       mul(1, 0, lo);
       mul(0, 1, lo);
     }
-    __syncthreads();  // every wave is done with the panel
-    float y[2][4];
+    float y[2][4], z = 0.0f;
 #pragma unroll
     for (int b = 0; b < 2; b++)
 #pragma unroll
-      for (int i = 0; i < 4; i++) y[b][i] = (hi[b][i] + lo[b][i]) + bt[b][i];
+      for (int i = 0; i < 4; i++) {
+        y[b][i] = (hi[b][i] + lo[b][i]) + bt[b][i];
+        z = fmaf(y[b][i], 0.0f, z);
+      }
+    const bool odd = __any(z != z);  // rare: an infinity or a NaN
+    if (odd) sp_whole_products(xv, pl, K8, K, NT, m, g, bt, y);
+    __syncthreads();  // every wave is done with the panel
     if (j + 1 < ntiles) {
       stage(j + 1);
       load_bt(a0 + T);
     }
-    {
-      const float* gl = gbuf + (j & 1) * T * T + m;
+    const float* gl = gbuf + (j & 1) * T * T + m;
+    if (odd) {
+      sp_phase2_whole(y, gl, eps, tw);
+    } else {
       float gr[8][2];
       sp_rows<0>(gr, gl);
       sp_phase2<0>(y, gr, gl, eps, tw);
+#pragma unroll
+      for (int b = 0; b < 2; b++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) y[b][i] = fmaxf(eps, y[b][i]);
     }
     // into operand order: row m, columns 8 g .. 8 g + 7
 #pragma unroll
     for (int b = 0; b < 2; b++)
 #pragma unroll
       for (int i = 0; i < 4; i++)
-        tr[(4 * g + i) * kTrP + 16 * b + m] = 16 * b + m < tw ? fmaxf(eps, y[b][i]) : 0.0f;
+        tr[(4 * g + i) * kTrP + 16 * b + m] = 16 * b + m < tw ? y[b][i] : 0.0f;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
