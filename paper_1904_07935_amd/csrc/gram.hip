@@ -385,6 +385,50 @@ __global__ __launch_bounds__(kThreads) void gram_partial_split(const float* __re
 #pragma unroll
       for (int j = 0; j < 2; j++) acc[0][i][j] += lo[i][j];
   }
+  // Rare: sums of the parts that are not finite (an infinite value's lower parts are
+  // NaN) are formed again from the values, on the FP32 matrix cores.
+#pragma unroll
+  for (int k = 0; k < UPW; k++) {
+    float z = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) z = fmaf(acc[k][i][j][e], 0.0f, z);
+    if (!has[k] || !__any(z != z)) continue;
+    const int half = lane >> 5, l = lane & 31;
+    // the share's rows: 16 of every stage (all of it where a stage is one share's)
+    constexpr int n = BK / KS;
+#pragma unroll 1
+    for (int i = 0; i < 2; i++)
+#pragma unroll 1
+      for (int j = 0; j < 2; j++) {
+        floatx16 x;
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[e] = 0.0f;
+        const int ca = 64 * pi[k] + 32 * i + l, cb = 64 * pj[k] + 32 * j + l;
+#pragma unroll 1
+        for (int64_t s0 = r0 + n * slice; s0 < r1; s0 += BK) {
+          float a[n / 2], b[n / 2];
+#pragma unroll
+          for (int q = 0; q < n / 2; q++) {
+            const int64_t r = s0 + 2 * q + half;
+            a[q] = r < r1 && ca < K ? X[r * K + ca] : 0.0f;
+            b[q] = r < r1 && cb < K ? X[r * K + cb] : 0.0f;
+          }
+#pragma unroll
+          for (int q = 0; q < n / 2; q++) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], x, 0, 0, 0);
+        }
+#pragma unroll
+        for (int ii = 0; ii < 2; ii++)
+#pragma unroll
+          for (int jj = 0; jj < 2; jj++)
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+              if (ii == i && jj == j && !isfinite(acc[k][ii][jj][e])) acc[k][ii][jj][e] = x[e];
+      }
+  }
   // lane holds C block row 8 jj + 4 h + ii, column lane % 32, in acc[4 jj + ii]
   const int h = lane >> 5, m = lane & 31;
   auto put_blocks = [&](int k, auto value) {

@@ -50,3 +50,26 @@ def test_single_products(cuda, D, K):
     Ht[D // 2 + 1] = 0.1 + torch.rand(K, generator=g, device=cuda)
     q, ref = _gram(cuda, D, K, Ht)
     assert float(((q - ref) / ref).abs().max()) <= 2.0 ** -23 * (1 + 2.0 ** -4)
+
+
+@pytest.mark.parametrize("V,K", [(65600, 64), (65600, 200), (65663, 400)])
+def test_not_finite(cuda, V, K):
+    """S of a W with an infinity and a value above the largest BF16: as the values' own
+    products give it, and bit for bit as before in the other columns."""
+    g = torch.Generator(device=cuda).manual_seed(V + K)
+    A = torch.rand(V, K + 3, generator=g, device=cuda)
+    plan = Plan(Matrix(V, K + 3, dense=A), torch.rand(V, K, generator=g, device=cuda) + 1e-3,
+                torch.rand(K + 3, K, generator=g, device=cuda))
+    plan.half("H")
+    clean = plan.intermediates()["S"].clone()
+    plan.W[5, 3], plan.W[V - 1, K - 2] = float("inf"), 3.4e38
+    ref = plan.W.double().T @ plan.W.double()
+    plan.half("H")
+    S = plan.intermediates()["S"].double()
+    plan.close()
+    assert torch.equal(torch.isinf(S), torch.isinf(ref.float()))
+    m = torch.isfinite(ref.float())
+    assert float(((S - ref)[m] / ref[m]).abs().max()) <= 2.0 ** -19
+    keep = torch.ones(K, dtype=torch.bool, device=cuda)
+    keep[3] = keep[K - 2] = False
+    assert torch.equal(S[keep][:, keep], clean[keep][:, keep].double())
