@@ -48,6 +48,15 @@ struct FoldWs {
   int L;
 };
 
+// The sizes of R' = A_new^T W on dense documents.
+void product_R(GemmArgs& g, int64_t Dn, int64_t V, int K) {
+  g.lda = V;
+  g.ldb = K;
+  g.M = Dn;
+  g.N = K;
+  g.Kd = V;
+}
+
 // `least`: the least workspace a fold-in can do with (R' of dense documents without
 // splits), for the library's own array, which has a fixed size.
 FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* AnewT, int hidden,
@@ -59,8 +68,10 @@ FoldWs fold_layout(void* base, int64_t Dn, int64_t V, int K, const nmf_matrix* A
   f.Qn = c.take<float>((size_t)K * K);
   size_t part = 1;
   if (AnewT->format == NMF_DENSE) {
-    const int sp = gemm_plan(Elem::F32, Dn, K, V, least ? 1 : 256).splits;
-    if (sp > 1) part = std::max(part, (size_t)sp * Dn * K);
+    GemmArgs g{};
+    product_R(g, Dn, V, K);
+    gemm_use(g, Elem::F32, least ? 1 : 256);
+    if (g.splits > 1) part = std::max(part, (size_t)g.splits * Dn * K);
   }
   f.partial = c.take<float>(part);
   f.gpart = c.take<float>(gram_partial_floats(K));
@@ -210,17 +221,13 @@ int plnmf::foldin_run(nmf_plan p, const nmf_matrix* AnewT, float* Ht_new, int in
     }
   } else {
     GemmArgs g{};
+    product_R(g, Dn, p->V, K);
     g.A = AnewT->dense;
-    g.lda = p->V;
     g.B = p->W;
-    g.ldb = K;
-    g.M = Dn;
-    g.N = K;
-    g.Kd = p->V;
     g.C = f.R;
     g.ldc = K;
     g.epi = EPI_STORE;
-    gemm_use(g, gemm_plan(Elem::F32, g.M, g.N, g.Kd, least ? 1 : 256));
+    gemm_use(g, Elem::F32, least ? 1 : 256);
     g.partial = f.partial;
     FCHECK(gemm(Elem::F32, false, false, g, s));
     if (objective) {

@@ -412,7 +412,7 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
   constexpr int BM = Tl::BM, BN = Tl::BN, BI = Tl::BI, BJ = Tl::BJ, BK = bk_of<T, CFG>();
   constexpr int NTHR = threads_of<CFG>(), NWN = BN / (32 * BJ), K8 = BK / 8, PL = parts_of<T>();
   constexpr bool F32 = sizeof(T) == 4;
-  constexpr int NB = Tl::BUFS, DIST = F32 || FAR || NB == 1 ? 1 : 2, STEPS = 2;
+  constexpr int NB = Tl::BUFS, DIST = F32 || NB == 1 ? 1 : 2, STEPS = 2;
   using SA = Stage<T, AT, FAR, BM, BK, NTHR>;
   using SB = Stage<T, !BT, FAR, BN, BK, NTHR>;
   constexpr int RPA = SA::RP, RPB = SB::RP, ABUF = PL * K8 * RPA, BUF = ABUF + PL * K8 * RPB;
@@ -680,17 +680,17 @@ hipError_t launch(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The form launched is the form set in `g`, however the operands are loaded:
-// the caller sizes and adds the tiles' sums (red_out, col_part) by it.
+// The form launched is the form planned: the caller sizes and adds the tiles' sums
+// (red_out, col_part) by it.
 template <typename T, bool AT, bool BT, bool FAR>
 hipError_t launch_form(const GemmArgs& g, hipStream_t s) {
   if (!epi_used<T, AT, BT>(g.epi)) return hipErrorInvalidValue;
-  switch (g.cfg) {
-    case 0: return launch<T, AT, BT, FAR, 0>(g, s);
-    case 1: return launch<T, AT, BT, FAR, 1>(g, s);
-    case 2: return launch<T, AT, BT, FAR, 2>(g, s);
-    default: return hipErrorInvalidValue;
+  if (g.cfg == 0) return launch<T, AT, BT, FAR, 0>(g, s);
+  if (g.cfg == 1) return launch<T, AT, BT, FAR, 1>(g, s);
+  if constexpr (!FAR) {
+    if (g.cfg == 2) return launch<T, AT, BT, FAR, 2>(g, s);
   }
+  return hipErrorInvalidValue;
 }
 
 template <typename T, bool FAR>
@@ -721,12 +721,12 @@ constexpr CfgCost kCfg[3] = {
 // contraction -- at the CU's rate shared by the workgroups on it, or at one
 // load latency per K-step where that is longer -- plus the time of writing and
 // summing the partial products.
-GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits) {
+GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits, bool far) {
   constexpr double kCus = 256.0, kBytesPerSec = 4.0e12;
   constexpr double kStart = 3.0e-6, kStep = 0.6e-6, kReduce = 3.0e-6;
   GemmPlan best{};
   double best_t = 0.0;
-  for (int c = 0; c < 3; c++) {
+  for (int c = 0; c < (far ? 2 : 3); c++) {
     const CfgCost& f = kCfg[c];
     const int bk = t == Elem::F32 ? f.bk32 : f.bk16;
     const double rate = t == Elem::F32 ? f.rate32 : f.rate16;
@@ -772,13 +772,18 @@ hipError_t splitk_reduce(const float* partial, int splits, int64_t M, int64_t N,
   return hipGetLastError();
 }
 
+// Dword-aligned rows within 32-bit tile offsets are loaded as dwords, others element
+// by element.
+bool gemm_far(Elem t, const GemmArgs& g) {
+  const size_t es = t == Elem::F32 ? 4 : 2;
+  return !aligned(g.A, 4) || !aligned(g.B, 4) || (g.lda * es) % 4 || (g.ldb * es) % 4 ||
+         g.lda >= (int64_t(1) << 22) || g.ldb >= (int64_t(1) << 22);
+}
+
 hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.epi == EPI_RESID_SQ && g.cfg != 0) return hipErrorInvalidValue;
-  // dword-aligned rows within 32-bit tile offsets; else element by element
-  const size_t es = t == Elem::F32 ? 4 : 2;
-  const bool far = !aligned(g.A, 4) || !aligned(g.B, 4) || (g.lda * es) % 4 || (g.ldb * es) % 4 ||
-                   g.lda >= (int64_t(1) << 22) || g.ldb >= (int64_t(1) << 22);
+  const bool far = gemm_far(t, g);
   const hipError_t e = t == Elem::F32 ? launch_type<float>(a_trans, b_trans, g, far, s)
                                       : launch_type<__bf16>(a_trans, b_trans, g, far, s);
   if (e != hipSuccess) return e;

@@ -97,18 +97,23 @@ enum class Elem { F32, BF16 };
 
 // Launch one GEMM with the tile form and splits set in `g`; returns hipError.
 // EPI_RESID_SQ takes form 0 (gemm_resid_tiles partial sums).  Not both
-// operands transposed.
+// operands transposed.  A form that the operands' loads don't have is refused.
 hipError_t gemm(Elem t, bool a_trans, bool b_trans, const GemmArgs& g, hipStream_t s);
 // Tile form and split-K factor (at most max_splits; the partial buffer holds
 // splits * M * N floats when splits > 1).
-GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits = 256);
+GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits = 256, bool far = false);
+// Whether the operands of `g` are loaded element by element (forms 0 and 1 only:
+// the `far` of gemm_plan).
+bool gemm_far(Elem t, const GemmArgs& g);
 int gemm_tile_cols(int cfg);  // columns of C that one workgroup computes
 int gemm_tile_rows(int cfg);
 int64_t gemm_resid_tiles(int64_t M, int64_t N);
 // C[M,N] (ldc) = sum_z partial[z] (+ bias[n])
 hipError_t splitk_reduce(const float* partial, int splits, int64_t M, int64_t N, float* C,
                          int64_t ldc, const float* bias, hipStream_t s);
-inline void gemm_use(GemmArgs& g, const GemmPlan& p) {
+// Plans the product set up in `g` (sizes and operands).
+inline void gemm_use(GemmArgs& g, Elem t, int max_splits) {
+  const GemmPlan p = gemm_plan(t, g.M, g.N, g.Kd, max_splits, gemm_far(t, g));
   g.cfg = p.cfg;
   g.splits = p.splits;
   g.k_per_split = p.k_per_split;

@@ -156,7 +156,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   g.epi = EPI_BIAS_GELU;
   g.bias = p.b1;
   g.C2 = w.gb;
-  gemm_use(g, gemm_plan(Elem::BF16, g.M, g.N, g.Kd, 1));
+  gemm_use(g, Elem::BF16, 1);
   MLPCHECK(gemm(Elem::BF16, false, true, g, s));
   // the output layer, its loss and dz2 = 2 / (b K) (yhat - y) softplus'(z2)
   GemmArgs g2{};
@@ -176,7 +176,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   g2.scale = (float)(2.0 / (double)(b * K));
   g2.red_out = w.red;
   g2.col_part = w.col2;
-  gemm_use(g2, gemm_plan(Elem::BF16, g2.M, g2.N, g2.Kd, 1));
+  gemm_use(g2, Elem::BF16, 1);
   MLPCHECK(gemm(Elem::BF16, false, true, g2, s));
   float* gW1 = grads;
   float* gb1 = gW1 + (size_t)H * K;
@@ -193,7 +193,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   a.Kd = b;
   a.ldc = H;
   a.epi = EPI_STORE;
-  gemm_use(a, gemm_plan(Elem::BF16, a.M, a.N, a.Kd, w.max_splits));
+  gemm_use(a, Elem::BF16, w.max_splits);
   a.C = a.splits > 1 ? nullptr : gW2;
   a.partial = w.partial;
   MLPCHECK(gemm(Elem::BF16, true, false, a, s));
@@ -212,7 +212,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   d.ldd = H;
   d.C2 = w.dz1b;
   d.col_part = w.col1;
-  gemm_use(d, gemm_plan(Elem::BF16, d.M, d.N, d.Kd, 1));
+  gemm_use(d, Elem::BF16, 1);
   MLPCHECK(gemm(Elem::BF16, false, false, d, s));
   // gW1 [H,K] = dz1^T x
   GemmArgs c{};
@@ -225,7 +225,7 @@ int loss_grad_rows(const Params& p, int K, int H, const float* X, const float* Y
   c.Kd = b;
   c.ldc = K;
   c.epi = EPI_STORE;
-  gemm_use(c, gemm_plan(Elem::BF16, c.M, c.N, c.Kd, w.max_splits));
+  gemm_use(c, Elem::BF16, w.max_splits);
   c.C = c.splits > 1 ? nullptr : gW1;
   c.partial = w.partial + (size_t)w.max_splits * K * H;
   MLPCHECK(gemm(Elem::BF16, true, false, c, s));
@@ -302,7 +302,7 @@ int mlp_forward_impl(const void* params, int K, int H, const float* X, float* Y,
     g.bias = p.b1;
     g.C2 = w.gb;
     g.ldc = H;
-    gemm_use(g, gemm_plan(Elem::BF16, g.M, g.N, g.Kd, 1));
+    gemm_use(g, Elem::BF16, 1);
     MLPCHECK(gemm(Elem::BF16, false, true, g, s));
     GemmArgs g2{};
     g2.A = w.gb;
@@ -316,7 +316,7 @@ int mlp_forward_impl(const void* params, int K, int H, const float* X, float* Y,
     g2.bias = p.b2;
     g2.C2 = Y + r * K;
     g2.ldc = K;
-    gemm_use(g2, gemm_plan(Elem::BF16, g2.M, g2.N, g2.Kd, 1));
+    gemm_use(g2, Elem::BF16, 1);
     MLPCHECK(gemm(Elem::BF16, false, true, g2, s));
   }
   return NMF_OK;

@@ -263,7 +263,7 @@ namespace {
 // Tile form and splits of a product, within the plan's partial buffer.
 void use_plan(nmf_plan_s* p, Elem t, GemmArgs& g) {
   const int64_t cap = std::max<int64_t>(1, (int64_t)p->partial_floats / (g.M * g.N));
-  gemm_use(g, gemm_plan(t, g.M, g.N, g.Kd, (int)std::min<int64_t>(cap, 256)));
+  gemm_use(g, t, (int)std::min<int64_t>(cap, 256));
   g.partial = p->partial;
 }
 
@@ -295,7 +295,6 @@ hipError_t product_R(nmf_plan_s* p) {
   g.C = p->R;
   g.ldc = K;
   g.epi = EPI_STORE;
-  use_plan(p, p->prec == NMF_BF16_PRODUCTS ? Elem::BF16 : Elem::F32, g);
   if (p->prec == NMF_BF16_PRODUCTS) {
     const int64_t ld = pad8(p->V);
     hipError_t e = cast_bf16_transpose(p->W, p->X_bf, p->V, K, ld, p->stream);  // W^T [K,V]
@@ -304,12 +303,14 @@ hipError_t product_R(nmf_plan_s* p) {
     g.lda = ld;
     g.B = p->X_bf;   // B(v,k) = WT[k*ld + v]
     g.ldb = ld;
+    use_plan(p, Elem::BF16, g);
     return gemm(Elem::BF16, false, true, g, p->stream);
   }
   g.A = p->A_dense;  // A(d,v) = A[v*D + d]
   g.lda = p->D;
   g.B = p->W;
   g.ldb = K;
+  use_plan(p, Elem::F32, g);
   return gemm(Elem::F32, true, false, g, p->stream);
 }
 
@@ -361,7 +362,6 @@ hipError_t product_P(nmf_plan_s* p, bool force_fp32, float* out) {
   g.C = out;
   g.ldc = K;
   g.epi = EPI_STORE;
-  use_plan(p, bf ? Elem::BF16 : Elem::F32, g);
   if (bf) {
     const int64_t ld = pad8(p->D);
     hipError_t e = cast_bf16_transpose(p->Ht, p->X_bf, p->D, K, ld, p->stream);  // H [K,D]
@@ -370,12 +370,14 @@ hipError_t product_P(nmf_plan_s* p, bool force_fp32, float* out) {
     g.lda = ld;
     g.B = p->X_bf;  // B(d,k) = H[k*ld + d]
     g.ldb = ld;
+    use_plan(p, Elem::BF16, g);
     return gemm(Elem::BF16, false, true, g, p->stream);
   }
   g.A = p->A_dense;
   g.lda = p->D;
   g.B = p->Ht;  // B(d,k) = Ht[d*K + k]
   g.ldb = K;
+  use_plan(p, Elem::F32, g);
   return gemm(Elem::F32, false, false, g, p->stream);
 }
 
@@ -493,7 +495,7 @@ hipError_t mu_update(nmf_plan_s* p, float* X, int64_t rows, float* N, const floa
   g.M = rows;
   g.N = K;
   g.Kd = K;
-  gemm_use(g, gemm_plan(Elem::F32, rows, K, K, 1));
+  gemm_use(g, Elem::F32, 1);
   const bool in_place = gemm_tile_cols(g.cfg) >= K;
   g.C = in_place ? X : N;
   g.ldc = K;
