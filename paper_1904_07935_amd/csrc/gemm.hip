@@ -482,7 +482,8 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
     };
     if constexpr (F32) {
       // One block after the other, its products in the order high, middle and low
-      // part of B; each part is read during the products of the part before.
+      // part of B; each part is read during the products of the part before.  The
+      // next row of blocks starts at the column where this one ends, whose B is there.
       constexpr int S = BK / 16;
       bf16x8 a[3][S], c[3][S];
       auto load_a = [&](int p, int i) {
@@ -500,12 +501,13 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
 #pragma unroll
       for (int i = 0; i < BI; i++) {
 #pragma unroll
-        for (int j = 0; j < BJ; j++) {
-          const bool last_j = j + 1 == BJ, last = last_j && i + 1 == BI;
+        for (int jj = 0; jj < BJ; jj++) {
+          const int j = i & 1 ? BJ - 1 - jj : jj;
+          const bool have_b = i > 0 && jj == 0, last_j = jj + 1 == BJ, last = last_j && i + 1 == BI;
           floatx16 hi;
 #pragma unroll
           for (int e = 0; e < 16; e++) hi[e] = 0.0f;
-          load_b(1, j);
+          if (!have_b) load_b(1, j);
 #pragma unroll
           for (int s = 0; s < S; s++) {
             mul(a[0][s], c[0][s], hi);
@@ -513,7 +515,7 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
             mul(a[1][s], c[0][s], lo[i][j]);
           }
           __builtin_amdgcn_sched_barrier(0);
-          load_b(2, j);
+          if (!have_b) load_b(2, j);
           if (last_j && !last) load_a(2, i + 1);
 #pragma unroll
           for (int s = 0; s < S; s++) {
@@ -521,7 +523,7 @@ __global__ __launch_bounds__(threads_of<CFG>(), 2) void gemm_kernel(GemmArgs g) 
             mul(a[1][s], c[1][s], lo[i][j]);
           }
           __builtin_amdgcn_sched_barrier(0);
-          if (!last) load_b(0, last_j ? 0 : j + 1);
+          if (!last_j) load_b(0, i & 1 ? j - 1 : j + 1);
           if (last_j && !last) load_a(1, i + 1);
 #pragma unroll
           for (int s = 0; s < S; s++) mul(a[0][s], c[2][s], lo[i][j]);
