@@ -45,7 +45,7 @@ struct SpmmKArgs {
   const void* X;
   float* out;
   float* carry;
-  int64_t n_items;
+  int64_t n_items, nnz;
   // without a host plan (n_rows > 0): waves of group_rows consecutive rows, then
   // seg_waves waves that share the *n_seg planned segments of the long rows
   int64_t n_rows;
@@ -103,6 +103,31 @@ __device__ __forceinline__ floatx4 ld_x4(const TX* row, int c, int K) {
   return r;
 }
 
+// The same, as they lie in memory: a conversion of a predicated load, next to it,
+// would wait for it.
+template <typename TX>
+struct Raw4 {
+  typedef TX T __attribute__((ext_vector_type(4)));
+};
+template <typename TX, bool VEC>
+__device__ __forceinline__ typename Raw4<TX>::T ld_raw4(const TX* row, int c, int K) {
+  typename Raw4<TX>::T r = {(TX)0.0f, (TX)0.0f, (TX)0.0f, (TX)0.0f};
+  if constexpr (!VEC) {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (c + e < K) r[e] = row[c + e];
+  } else if constexpr (sizeof(TX) == 4) {
+    if (c < K) r = *(const any4*)(row + min(c, K - 4));
+  } else {
+    if (c < K) r = *(const bf16x4*)(row + c);
+  }
+  return r;
+}
+template <typename T>
+__device__ __forceinline__ floatx4 to_floats(T x) {
+  return floatx4{(float)x[0], (float)x[1], (float)x[2], (float)x[3]};
+}
+
 constexpr int kMaxRowsPerItem = 256;
 constexpr int kFlatMaxNnz = 128;  // item nonzeros the flat kernel prefetches
 
@@ -153,28 +178,31 @@ __device__ __forceinline__ void wave_items(const SpmmKArgs& a, F work) {
 }
 
 // The item's nonzeros row by row, NPAR side by side.  Few items are in flight on
-// small inputs, so a row's chain of loads sets the time: eight gathers a step,
+// small inputs, so a row's chain of loads sets the time: UNR gathers a step,
 // the indices of the next step (of the next row, at a row's end) read one step
 // ahead, and the last step of a row filled up with zeros (0 * 0 added leaves a
-// sum as it is) instead of taken one nonzero at a time.  On 6,037 x
-// 2,741 with 165,000 nonzeros at K = 77 (both products), with the items of half the
-// size that spmm_build makes there: 43 -> 22 us.
-template <int VPL, int LPN, typename TV, typename TX, bool VEC>
+// sum as it is) instead of taken one nonzero at a time.  BF16 values and rows stay as
+// they are loaded until they are used.  Ranks of 33 to 128: eight gathers a step below
+// 524,288 nonzeros, where the chain is what there is; four above, where waves in
+// flight count more and eight take half as many registers again (FP32 / BF16, one
+// product, before / eight / four: 6,037 x 2,741 with 165,000 nonzeros, K = 100, 20 / 11.5 /
+// 13 and 31 / 16 / 17.5 us; 60,000 x 60,000 with 4.5 million, K = 96, 134 / 143 / 133 and
+// 181 / 146 / 144 us).
+template <int VPL, int LPN, typename TV, typename TX, bool VEC, int UNR>
 __device__ __forceinline__ void items_wave(const SpmmKArgs& a, const int4 item, const int slot) {
   constexpr int NPAR = 64 / LPN;  // nonzeros processed side by side per wave
-  constexpr int UNR = VPL == 1 && LPN >= 16 ? 8 : 4;
   const int lane = threadIdx.x & 63;
   const int grp = lane / LPN, q = lane % LPN;
   const int K = a.K;
   const TX* X = (const TX*)a.X;
   int32_t cc[UNR];
-  float vv[UNR];
+  TV vv[UNR];
   auto fetch = [&](int64_t j, int64_t end) {
 #pragma unroll
     for (int u = 0; u < UNR; u++) {
       const bool in = j + u * NPAR < end;
       cc[u] = in ? a.col[j + u * NPAR] : -1;
-      vv[u] = in ? ld_val<TV>(a.val, j + u * NPAR) : 0.0f;
+      vv[u] = in ? ((const TV*)a.val)[j + u * NPAR] : (TV)0.0f;
     }
   };
   int64_t rs = item.z, re = min(a.rowptr[item.x + 1], item.w);
@@ -186,15 +214,16 @@ __device__ __forceinline__ void items_wave(const SpmmKArgs& a, const int4 item, 
     for (int v = 0; v < VPL; v++) acc[v] = floatx4{0, 0, 0, 0};
     if (rs == re) fetch(re + grp, re2);
     while (rs < re) {
-      floatx4 x[UNR][VPL];
-      float w[UNR];
+      typename Raw4<TX>::T x[UNR][VPL];
+      TV w[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; u++) {
         w[u] = vv[u];
 #pragma unroll
-        for (int v = 0; v < VPL; v++)
-          x[u][v] = cc[u] >= 0 ? ld_x4<TX, VEC>(X + (int64_t)cc[u] * a.ldx, 4 * (q + LPN * v), K)
-                               : floatx4{0, 0, 0, 0};
+        for (int v = 0; v < VPL; v++) {
+          x[u][v] = typename Raw4<TX>::T{(TX)0.0f, (TX)0.0f, (TX)0.0f, (TX)0.0f};
+          if (cc[u] >= 0) x[u][v] = ld_raw4<TX, VEC>(X + (int64_t)cc[u] * a.ldx, 4 * (q + LPN * v), K);
+        }
       }
       rs += UNR * NPAR;
       if (rs < re) fetch(rs + grp, re);
@@ -202,7 +231,7 @@ __device__ __forceinline__ void items_wave(const SpmmKArgs& a, const int4 item, 
 #pragma unroll
       for (int u = 0; u < UNR; u++)
 #pragma unroll
-        for (int v = 0; v < VPL; v++) acc[v] += w[u] * x[u][v];
+        for (int v = 0; v < VPL; v++) acc[v] += (float)w[u] * to_floats(x[u][v]);
     }
     rs = re;
     re = re2;
@@ -221,9 +250,11 @@ __device__ __forceinline__ void items_wave(const SpmmKArgs& a, const int4 item, 
   }
 }
 
-template <int VPL, int LPN, typename TV, typename TX, bool VEC, bool PLANNED>
+template <int VPL, int LPN, typename TV, typename TX, bool VEC, bool PLANNED, int UNR>
 __global__ __launch_bounds__(256) void spmm_items(SpmmKArgs a) {
-  wave_items<PLANNED>(a, [&](const int4 item, const int slot) { items_wave<VPL, LPN, TV, TX, VEC>(a, item, slot); });
+  wave_items<PLANNED>(a, [&](const int4 item, const int slot) {
+    items_wave<VPL, LPN, TV, TX, VEC, UNR>(a, item, slot);
+  });
 }
 
 // Element k of a register array spread over the wave (element 64 m + l in lane
@@ -408,24 +439,34 @@ unsigned blocks_of(const SpmmKArgs& a) {
 
 // FP32 products: 16-byte rows at every rank but 1 .. 3 (LPN 1); only these go
 // without a host plan
-template <int VPL, int LPN, typename TV, typename TX>
-hipError_t launch_t(const SpmmKArgs& a, bool vec, hipStream_t s) {
+template <int VPL, int LPN, int UNR, typename TV, typename TX>
+hipError_t launch_u(const SpmmKArgs& a, bool vec, hipStream_t s) {
   const unsigned blocks = blocks_of(a);
   if (blocks == 0) return hipSuccess;
   if constexpr (sizeof(TX) == 4) {
     if (LPN == 1 && !vec) {
-      if (a.n_rows > 0) spmm_items<1, 1, TV, TX, false, false><<<blocks, 256, 0, s>>>(a);
-      else spmm_items<1, 1, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
+      if (a.n_rows > 0) spmm_items<1, 1, TV, TX, false, false, UNR><<<blocks, 256, 0, s>>>(a);
+      else spmm_items<1, 1, TV, TX, false, true, UNR><<<blocks, 256, 0, s>>>(a);
     } else if (a.n_rows > 0) {
-      spmm_items<VPL, LPN, TV, TX, true, false><<<blocks, 256, 0, s>>>(a);
+      spmm_items<VPL, LPN, TV, TX, true, false, UNR><<<blocks, 256, 0, s>>>(a);
     } else {
-      spmm_items<VPL, LPN, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
+      spmm_items<VPL, LPN, TV, TX, true, true, UNR><<<blocks, 256, 0, s>>>(a);
     }
   } else {
-    if (vec) spmm_items<VPL, LPN, TV, TX, true, true><<<blocks, 256, 0, s>>>(a);
-    else spmm_items<VPL, LPN, TV, TX, false, true><<<blocks, 256, 0, s>>>(a);
+    if (vec) spmm_items<VPL, LPN, TV, TX, true, true, UNR><<<blocks, 256, 0, s>>>(a);
+    else spmm_items<VPL, LPN, TV, TX, false, true, UNR><<<blocks, 256, 0, s>>>(a);
   }
   return hipGetLastError();
+}
+
+constexpr int64_t kFewNnz = 4096 * kFlatMaxNnz;  // below, less than a full item per wave slot
+
+template <int VPL, int LPN, typename TV, typename TX>
+hipError_t launch_t(const SpmmKArgs& a, bool vec, hipStream_t s) {
+  if constexpr (VPL == 1 && LPN >= 16) {
+    if (a.nnz < kFewNnz) return launch_u<VPL, LPN, 8, TV, TX>(a, vec, s);
+  }
+  return launch_u<VPL, LPN, 4, TV, TX>(a, vec, s);
 }
 
 template <int VPL, typename TV, typename TX>
@@ -565,6 +606,7 @@ hipError_t spmm_slice(const SpmmPlan& p, Elem t, const void* X0, int64_t ldx, in
   a.out = out;
   a.carry = p.carry;
   a.n_items = p.n_items;
+  a.nnz = p.nnz;
   a.K = K;
   const bool vec = t == Elem::F32 ? K >= 4 : K % 4 == 0 && ldx % 4 == 0 && ldo % 4 == 0 &&
                                                 (uintptr_t)X % 8 == 0 && (uintptr_t)out % 16 == 0 &&
@@ -601,6 +643,7 @@ hipError_t spmm_unplanned(const SpmmPlan& p, const int32_t* counts, const float*
   a.out = out;
   a.carry = p.carry;
   a.n_rows = p.rows;
+  a.nnz = p.nnz;
   // rows per wave: as many as about one full item holds
   const int64_t mean = p.nnz / p.rows;
   a.group_rows = (int)std::max<int64_t>(1, std::min<int64_t>(kFlatMaxNnz / std::max<int64_t>(mean, 1), 32));
