@@ -390,7 +390,8 @@ __global__ __launch_bounds__(256) void spmm_flat(SpmmKArgs a) {
 // order for a given K and segment count, so results are bitwise reproducible.
 constexpr int kFixThreads = 512;
 
-__global__ __launch_bounds__(kFixThreads) void spmm_fixup(const int32_t* __restrict__ fix,
+template <bool VEC>
+__global__ __launch_bounds__(kFixThreads, 8) void spmm_fixup(const int32_t* __restrict__ fix,
                                                           int64_t n_fix,
                                                           const int32_t* __restrict__ n_fix_dev,
                                                           const float* __restrict__ carry,
@@ -402,14 +403,12 @@ __global__ __launch_bounds__(kFixThreads) void spmm_fixup(const int32_t* __restr
   const int S = kFixThreads / nv > 0 ? kFixThreads / nv : 1;
   const int t = threadIdx.x;
   const int v = t % nv, sl = t / nv;
-  const bool vec = K >= 4;
   for (int64_t i = blockIdx.x; i < n_fix; i += gridDim.x) {
     const int64_t r = fix[3 * i], first = fix[3 * i + 1], cnt = fix[3 * i + 2];
     floatx4 acc = floatx4{0, 0, 0, 0};
     if (sl < S && t < nv * S) {
       auto seg = [&](int64_t g) -> floatx4 {
-        const float* p = carry + (first + g) * K;
-        return vec ? ld_x4<float, true>(p, 4 * v, K) : ld_x4<float, false>(p, 4 * v, K);
+        return ld_x4<float, VEC>(carry + (first + g) * K, 4 * v, K);
       };
       int64_t g = sl;
       for (; g + 3 * S < cnt; g += 4 * S) {
@@ -425,11 +424,19 @@ __global__ __launch_bounds__(kFixThreads) void spmm_fixup(const int32_t* __restr
     __syncthreads();
     if (sl == 0 && t < nv) {
       floatx4 tot = part[v];
-      for (int k = 1; k < S; k++) tot += part[k * nv + v];
-      st_x4(out + r * ldo, 4 * v, K, vec, tot);
+      const int used = cnt < S ? (int)cnt : S;  // slices that had a segment
+      for (int k = 1; k < used; k++) tot += part[k * nv + v];
+      st_x4(out + r * ldo, 4 * v, K, VEC, tot);
     }
     __syncthreads();  // `part` is written again for the next row
   }
+}
+
+hipError_t launch_fixup(unsigned blocks, const int32_t* fix, int64_t n_fix, const int32_t* n_fix_dev,
+                        const float* carry, float* out, int K, int64_t ldo, hipStream_t s) {
+  if (K >= 4) spmm_fixup<true><<<blocks, kFixThreads, 0, s>>>(fix, n_fix, n_fix_dev, carry, out, K, ldo);
+  else spmm_fixup<false><<<blocks, kFixThreads, 0, s>>>(fix, n_fix, n_fix_dev, carry, out, K, ldo);
+  return hipGetLastError();
 }
 
 unsigned blocks_of(const SpmmKArgs& a) {
@@ -617,8 +624,7 @@ hipError_t spmm_slice(const SpmmPlan& p, Elem t, const void* X0, int64_t ldx, in
                                 : launch_k<__bf16, __bf16>(a, vec, vec8, flat, s);
   if (e != hipSuccess) return e;
   if (p.n_fix > 0) {
-    spmm_fixup<<<(unsigned)p.n_fix, kFixThreads, 0, s>>>(p.fix, p.n_fix, nullptr, p.carry, out, K, ldo);
-    e = hipGetLastError();
+    e = launch_fixup((unsigned)p.n_fix, p.fix, p.n_fix, nullptr, p.carry, out, K, ldo, s);
   }
   return e;
 }
@@ -653,9 +659,7 @@ hipError_t spmm_unplanned(const SpmmPlan& p, const int32_t* counts, const float*
   a.K = K;
   hipError_t e = launch_k<float, float>(a, K >= 4, false, true, s);
   if (e != hipSuccess || most == 0) return e;
-  spmm_fixup<<<(unsigned)std::min<int64_t>(most, 512), kFixThreads, 0, s>>>(p.fix, 0, counts + 1, p.carry,
-                                                                          out, K, K);
-  return hipGetLastError();
+  return launch_fixup((unsigned)std::min<int64_t>(most, 512), p.fix, 0, counts + 1, p.carry, out, K, K, s);
 }
 
 // ------------------------------------------------------- CSR transpose ----
