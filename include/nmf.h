@@ -218,9 +218,12 @@ int nmf_foldin(nmf_plan plan, const nmf_matrix* AnewT, float* Ht_new, int init_m
  * is loaded on that GPU and held until the process ends; its address is looked
  * up on the first call on each device.  Arguments, results and errors are those
  * of nmf_foldin, plus:
- *   NMF_E_WORKSPACE  nmf_foldin_workspace_bytes() for these documents exceeds
- *                    NMF_NOALLOC_SCRATCH_BYTES (fold the documents in smaller
- *                    batches, or call nmf_foldin);
+ *   NMF_E_WORKSPACE  the documents do not fit NMF_NOALLOC_SCRATCH_BYTES (fold
+ *                    them in smaller batches, or call nmf_foldin).  Documents
+ *                    whose nmf_foldin_workspace_bytes() does not exceed it always
+ *                    fit; dense ones beyond it run as long as they fit without the
+ *                    partial sums of A_new^T W, which is then formed in one pass:
+ *                    its sums are added in another order than nmf_foldin's;
  *   NMF_E_ARG        the current device is not the plan's.
  * The call allocates no device memory.  Every call on a GPU uses the same
  * array and leaves its contents behind (each call clears what it needs

@@ -21,17 +21,19 @@
 // half, without bank conflicts, whichever way the operand lies in memory.  The
 // split runs once per element on the way from registers to LDS.
 // Output block layout: lane l holds C[8j + 4(l/32) + i][l%32], j,i < 4.
-// Split-K writes FP32 partials that a fixed-order pass sums (deterministic).
+// Split-K writes FP32 partials that a pass adds in 64 bits and in a fixed order
+// (deterministic).
 //
-// What bounds it and what it measured (against the 128 x 128 kernel on the FP32
-// matrix cores that it replaced; same box): 10,000 x 240 x 10,000 FP32 550 ->
-// 330 us per product, with the splitting (about 5.5 VALU instructions per
-// element) and the matrix cores each near half of the time; the dense-row block
-// (256 x 400 x 300,000) 715 -> 430 us; BF16 10,000 x 240 x 10,000 121 -> 80 us,
-// bound by the latency of the operand loads; 800 x 16 x 1,000 35 -> 10 us and
-// 4,096 x 100 x 100 17 -> 7.5 us, latency (small tiles, more splits).  Errors
-// against 64 bits, RMS over sampled elements, old / new: 9.5e-8 / 9.5e-8 at
-// 10,000 terms, 6.0e-8 / 4.7e-8 at 100, 1.3e-7 / 1.3e-7 at 300,000.
+// What bounds it and what it measured (kernel times, against the 128 x 128 kernel
+// on the FP32 matrix cores that it replaced, same box): 10,000 x 240 x 10,000 FP32
+// 502 -> 335 us (A H^T) and 488 -> 319 us (A^T W), with the splitting (about 5.5
+// VALU instructions per element), the LDS and the matrix cores each near half of
+// the time or above; the dense-row block (256 x 400 x 300,000) 707 -> 417 us; BF16
+// 10,000 x 240 x 10,000 127 -> 92 us, bound by the latency of the operand loads;
+// 1,000 x 16 x 800 33 and 28 -> 8.5 and 8 us, 4,096 x 100 x 100 32 -> 13 us,
+// latency (small tiles, more splits).  Errors against 64 bits, RMS over all
+// elements, FP32 matrix cores / here: 9.5e-8 / 9.4e-8 at 10,000 terms, 5.3e-8 /
+// 2.7e-8 at 3,000, 6.6e-8 / 5.5e-8 at 100, 2.5e-8 / 2.6e-8 for single products.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -56,7 +58,7 @@ struct Tile<1> {  // few outputs: more workgroups
   static constexpr int BM = 64, BN = 64, BI = 1, BJ = 1, BK32 = 32, BK16 = 64, BUFS = 1;
 };
 template <>
-struct Tile<2> {  // at most 32 columns
+struct Tile<2> {  // few tiles of 128 x 128, or narrow outputs
   static constexpr int BM = 128, BN = 32, BI = 1, BJ = 1, BK32 = 32, BK16 = 64, BUFS = 2;
 };
 template <int CFG>
@@ -706,6 +708,10 @@ hipError_t launch_type(bool a_trans, bool b_trans, const GemmArgs& g, bool far, 
   return far ? launch_elem<T, true>(a_trans, b_trans, g, s) : launch_elem<T, false>(a_trans, b_trans, g, s);
 }
 
+// The forms as gemm_plan sees them: `occ` workgroups fit on a CU (by LDS and
+// registers), and a full CU then runs at about `rate` (FP32 and BF16 products: 159 and
+// 666 TFLOP/s over the chip for form 0, where 10,000 x 240 x 10,000 reaches 143 to 150
+// and 520 with its start and end; what the choice depends on is the forms' ratio).
 struct CfgCost {
   int BM, BN, bk32, bk16, occ;
   double rate32, rate16;  // FLOP/s of one full CU
@@ -722,7 +728,11 @@ constexpr CfgCost kCfg[3] = {
 // of workgroups over the chip's slots times one split's share of the
 // contraction -- at the CU's rate shared by the workgroups on it, or at one
 // load latency per K-step where that is longer -- plus the time of writing and
-// summing the partial products.
+// summing the partial products.  A form is not tied to a width: the 128 x 32 one is
+// chosen where its tiles fill the CUs better (rows x 512 or x 200 columns at two to
+// four thousand rows), and 16 columns may well go to the 64 x 64 one.  kCus is the
+// MI355X's CU count, not the device's, so that a product's sums, which the split
+// decides, are the same on a partition.
 GemmPlan gemm_plan(Elem t, int64_t M, int64_t N, int64_t Kd, int max_splits, bool far) {
   constexpr double kCus = 256.0, kBytesPerSec = 4.0e12;
   constexpr double kStart = 3.0e-6, kStep = 0.6e-6, kReduce = 3.0e-6;

@@ -33,8 +33,8 @@
 // are added in the LDS in a fixed order.  Wider Grams give each wave two units.
 // Workgroups along y take different units of the same rows, so that a chunk's
 // partial (4 K^2 bytes or so, against 4 K rows of input) stays small against its
-// rows.  300,000 x 400: 693 -> 353 us, 100,000 x 400: 238 -> 121 us (FP32 before,
-// split after); the matrix cores are busy a little over half of that.
+// rows.  300,000 x 400: 688 -> 373 us, 100,000 x 400: 240 -> 130 us (FP32 before,
+// split after); the matrix cores are busy about half of that.
 #include <algorithm>
 
 #include "bf16x3.hpp"

@@ -881,8 +881,8 @@ hipError_t h_rows_dispatch(const HalsArgs& b, bool vec, hipStream_t s) {
 // row), and one wave's phase 2 fills the other's matrix-core time.  Bounds: the
 // LDS reads of the panel (every wave reads all of it: 3 KB per 96 matrix-core
 // cycles) and the matrix cores are about equal, then phase 2.  Measured on
-// 300,000 x 400: 1,410 -> 960 us (FP32 rows kernel before); 100,000 x 200: 222 ->
-// 140 us.  Per tile at K = 400, cycles of both waves of a SIMD: product 9,300 (7,900
+// 300,000 x 400: 1,430 -> 970 us (FP32 rows kernel before); 100,000 x 200: 226 ->
+// 143 us.  Per tile at K = 400, cycles of both waves of a SIMD: product 9,300 (7,900
 // with the panel reads left out), phase 2 5,000, the rest 1,500.  Error of an
 // update against 64 bits, Frobenius, rows kernel / this one: 100,000 x 200 1.8e-6 /
 // 6.9e-7, 65,537 x 400 2.5e-6 / 9.3e-7.
@@ -1778,15 +1778,22 @@ const void* w_kernel_for(int rpt, bool vec, bool local) {
 
 int hals_rows_per_group_h() { return kRowsH; }
 
+// The LDS beside a workgroup's rows and panel that the rule below counts.  It is more
+// than the kernel takes (5,248 floats), and stands for what the hardware allots: with
+// it the rule's two workgroups a CU at K = 121 .. 128 are what is resident (three
+// would need 163,200 bytes of 163,840, which do not fit its granules).
+constexpr int kHLdsBeside = 5472;
+
 // Which H-update kernel.  The rows-in-registers kernel takes 128 rows per
 // workgroup and fills the chip from about 256 x 128 rows on.  Below that the
 // LDS-resident kernel (32 rows per workgroup) keeps more CUs busy, as long as
 // all its workgroups are resident at once; once they need a second round (its
 // LDS holds two workgroups per CU up to K = 224, one above), the rows kernel's
-// single round is no longer than two.  Measured (LDS / rows, us): K = 200, 10,000
-// rows 39 / 58, 16,000 rows 40 / 59, 20,000 rows 64 / 60; K = 240, 8,192 rows
-// 38 / 69, 10,000 rows 70 / 70, 20,000 rows 104 / 71; K = 400, 8,192 rows 84 / 140,
-// 10,000 rows 156 / 141.
+// single round is no longer than two.  Measured (LDS / rows, us): K = 64, 24,500 rows
+// 15 / 15, 26,000 rows 20 / 15; K = 120, 24,500 rows 26 / 33, 26,000 rows 37 / 33;
+// K = 128, 15,000 rows 22 / 30, 16,500 rows 35 / 30; K = 200, 12,000 rows 38 / 59,
+// 16,500 rows 63 / 59; K = 240, 8,192 rows 38 / 69, 10,000 rows 70 / 70, 20,000 rows
+// 104 / 71; K = 400, 8,192 rows 84 / 140, 10,000 rows 156 / 141.
 // NMF_H_KERNEL=rows|lds forces one (read when the half starts: measurement,
 // tests).
 static bool h_rows_kernel_for(int64_t rows, int K, int cus) {
@@ -1795,8 +1802,11 @@ static bool h_rows_kernel_for(int64_t rows, int K, int cus) {
     if (e[0] == 'l') return false;
   }
   if (rows >= 32768) return true;
-  // the LDS kernel's workgroups per CU, by 5,472 floats beside its rows and panel
-  const size_t floats = (size_t)kRowsH * h_xp(K) + (size_t)kpad(K) * TP + 5472;
+  // the LDS kernel's workgroups per CU, by LDS (up to K = 64 it counts four or more,
+  // where registers allow three: from 24,577 rows to 32,767 the rows kernel would be
+  // 1 to 5 us quicker, but its sums are another order's, and corpora of that size
+  // keep the trajectory they have)
+  const size_t floats = (size_t)kRowsH * h_xp(K) + (size_t)kpad(K) * TP + kHLdsBeside;
   const int64_t per_cu = (int64_t)(kRrLdsMax / (floats * 4));
   const int64_t groups = (rows + kRowsH - 1) / kRowsH;
   return groups > (int64_t)(cus > 0 ? cus : 256) * per_cu;
